@@ -13,13 +13,17 @@
 //          sum — logits stay in registers and never reach memory;
 //   PARTIAL float32 split-K slice, folded into the residual stream by the next RMSNorm;
 //   F32    plain float32 store (debug logits).
-// Tiles: BW weight rows x BT tokens per workgroup, K staged through a multi-stage LDS ring of
-// 64- or 128-deep slices filled by direct-to-LDS DMA (gemm_kernel), or through registers
-// (gemm_rp_kernel). The unit -> workgroup map is XCD-aware: consecutive tiles (which share a
-// weight tile) land on the same XCD and its L2. The configuration of each GEMM shape comes from a
-// measured table (gemm_tuned.inc), other shapes from a cost model.
+// Tiles: BW weight rows x BT tokens per workgroup, K staged through a multi-stage LDS ring of 64-deep
+// slices filled by direct-to-LDS DMA. Two kernels: gemm_pp_kernel, whose two waves per SIMD alternate
+// between reading and multiplying (the large tiles), and gemm_kernel (few tokens, K tails). The unit ->
+// workgroup map is XCD-aware: tiles that share operands land on the same XCD and its L2. The
+// configuration comes from a cost model with measured constants per configuration (gemm_tuned.inc).
 #include <float.h>
 #include <limits.h>
+
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
 
 #include "dcl_internal.h"
 
@@ -31,17 +35,20 @@ __device__ __forceinline__ f32x4_t mfma16(const bf16x8_t& a, const bf16x8_t& b, 
 }
 
 // ---------------------------------------------------------------- epilogues
-// apply(): acc[i][j] holds C[wb + 16 i + 4 (lane/16) + r][tb + 16 j + lane%16], r = 0..3.
+// apply(): acc[i][j] holds C[wb + 16 i + 4 (lane/16) + r][tb + 16 JS j + lane%16], r = 0..3 (JS: the stride
+// of a wave's token fragments, in fragments).
+
+enum { kEpiPlain, kEpiLm, kEpiDebug };
 
 struct EpiResid {
   float* r;
-  static constexpr bool kPartial = false;
-  template <int SW, int ST>
+  static constexpr int kKind = kEpiPlain;
+  template <int SW, int ST, int JS = 1>
   __device__ __forceinline__ void apply(f32x4_t (&acc)[SW][ST], int wb, int tb, int lane, int Nw, int T, int, int) const {
     const int wq = wb + 4 * (lane >> 4), tl = tb + (lane & 15);
 #pragma unroll
     for (int j = 0; j < ST; ++j) {
-      const int t = tl + 16 * j;
+      const int t = tl + 16 * JS * j;
       if (t >= T) continue;
 #pragma unroll
       for (int i = 0; i < SW; ++i) {
@@ -58,14 +65,14 @@ struct EpiResid {
 
 struct EpiSwiglu {
   bf16_t* a;  // [T, Nw/2]
-  static constexpr bool kPartial = false;
-  template <int SW, int ST>
+  static constexpr int kKind = kEpiPlain;
+  template <int SW, int ST, int JS = 1>
   __device__ __forceinline__ void apply(f32x4_t (&acc)[SW][ST], int wb, int tb, int lane, int Nw, int T, int, int) const {
     const int F = Nw >> 1;
     const int wq = wb + 4 * (lane >> 4), tl = tb + (lane & 15);
 #pragma unroll
     for (int j = 0; j < ST; ++j) {
-      const int t = tl + 16 * j;
+      const int t = tl + 16 * JS * j;
       if (t >= T) continue;
 #pragma unroll
       for (int i = 0; i < SW; ++i) {
@@ -81,20 +88,18 @@ struct EpiSwiglu {
 };
 
 // Offsets are 32-bit element counts: gemm_qkv rejects outputs of 2^31 elements or more.
-template <int DH>
 struct EpiQkv {
   QkvOut o;
-  static constexpr bool kPartial = false;
-  template <int SW, int ST>
+  static constexpr int kKind = kEpiPlain;
+  template <int SW, int ST, int JS = 1>
   __device__ __forceinline__ void apply(f32x4_t (&acc)[SW][ST], int wb, int tb, int lane, int Nw, int T, int, int) const {
-    constexpr int HALF = DH / 2, LOG2DH = DH == 128 ? 7 : 6;
-    static_assert(DH == 64 || DH == 128, "head_dim");
+    const int DH = o.dh, HALF = DH >> 1, LOG2DH = DH == 128 ? 7 : 6;  // head_dim 64 or 128
     const int qrows = o.H * DH, krows = o.Hkv * DH;
     const int Sk = o.Sk ? o.Sk : o.S;  // fresh key rows per (sequence, kv head); token s sits in slot koff + s
     const int wq = wb + 4 * (lane >> 4), tl = tb + (lane & 15);
 #pragma unroll
     for (int j = 0; j < ST; ++j) {
-      const int t = tl + 16 * j;
+      const int t = tl + 16 * JS * j;
       if (t >= T) continue;
       const int b = t / o.S, s = t - b * o.S;
       const int pos = o.pos0 + s;
@@ -143,13 +148,13 @@ struct EpiQkv {
 
 struct EpiF32 {
   float* out;
-  static constexpr bool kPartial = false;
-  template <int SW, int ST>
+  static constexpr int kKind = kEpiDebug;
+  template <int SW, int ST, int JS = 1>
   __device__ __forceinline__ void apply(f32x4_t (&acc)[SW][ST], int wb, int tb, int lane, int Nw, int T, int, int) const {
     const int wq = wb + 4 * (lane >> 4), tl = tb + (lane & 15);
 #pragma unroll
     for (int j = 0; j < ST; ++j) {
-      const int t = tl + 16 * j;
+      const int t = tl + 16 * JS * j;
       if (t >= T) continue;
 #pragma unroll
       for (int i = 0; i < SW; ++i)
@@ -167,15 +172,15 @@ struct EpiF32 {
 struct EpiPartial {
   float* P;
   size_t stride;
-  static constexpr bool kPartial = true;
-  template <int SW, int ST>
+  static constexpr int kKind = kEpiPlain;
+  template <int SW, int ST, int JS = 1>
   __device__ __forceinline__ void apply(f32x4_t (&acc)[SW][ST], int wb, int tb, int lane, int Nw, int T, int,
                                         int split) const {
     float* base = P + (size_t)split * stride;
     const int wq = wb + 4 * (lane >> 4), tl = tb + (lane & 15);
 #pragma unroll
     for (int j = 0; j < ST; ++j) {
-      const int t = tl + 16 * j;
+      const int t = tl + 16 * JS * j;
       if (t >= T) continue;
 #pragma unroll
       for (int i = 0; i < SW; ++i) {
@@ -195,7 +200,6 @@ struct Part {
   float m1, m2, s, t;  // s = sum exp(l - m1), t = sum exp(l - m1) (l - m1), both relative to m1
   int i1, i2;
 };
-constexpr size_t kLmEpiLds = sizeof(Part) * kLmWaves * 256;  // static LDS of the LM-head epilogue
 __device__ __forceinline__ void top2_push(Part& p, float v, int id) {
   if (better(v, id, p.m1, p.i1)) {
     p.m2 = p.m1; p.i2 = p.i1; p.m1 = v; p.i1 = id;
@@ -229,19 +233,22 @@ __device__ __forceinline__ Part part_merge(const Part& a, const Part& b) {
 template <int BW, int WW>
 struct EpiLm {
   LmOut o;
-  static constexpr bool kPartial = false;
-  // [wave along W][token within the workgroup tile] (BT <= 256); only the split-tile layout uses it
-  __device__ static Part (*xch_slot())[256] {
-    __shared__ Part xch[WW][256];
+  static constexpr int kKind = kEpiLm;
+  // [wave along W][token fragment slot within the workgroup tile]; only the split-tile layout uses it
+  template <int NTOK>
+  __device__ static Part (*xch_slot())[NTOK] {
+    __shared__ Part xch[WW][NTOK];
     return xch;
   }
-  template <int SW, int ST>
+  template <int SW, int ST, int JS = 1>
   __device__ __forceinline__ void apply(f32x4_t (&acc)[SW][ST], int wb, int tb, int lane, int Nw, int T, int tile_w, int) const {
     constexpr bool kOwn = 16 * SW == kLmTile;  // this wave covers a whole vocabulary tile
     // any other layout is never planned for the LM head (plan_gemm's lm_ok); nothing to instantiate
     if constexpr (!kOwn && !(BW == kLmTile && 16 * SW * WW == BW)) return;
     const int wid = threadIdx.x >> 6;
-    const int wave_w = wid % WW, wave_t = wid / WW;
+    // the wave grids of gemm_kernel (JS = 1) and gemm_pp_kernel (token fragments JS apart)
+    const int wave_w = JS == 1 ? wid % WW : wid / JS, wave_t = JS == 1 ? wid / WW : wid % JS;
+    constexpr int NTOK = ST * 16 * (8 / WW);  // tokens of the workgroup tile (8 waves)
     const int R = *o.count;
     const int vt = kOwn ? wb / kLmTile : tile_w;  // vocabulary tile of this wave's partial
     const int wq = wb + 4 * (lane >> 4), tl = tb + (lane & 15);
@@ -285,23 +292,23 @@ struct EpiLm {
       p.s = s;
       p.t = t;
       if constexpr (kOwn || WW == 1) {
-        const int t = tl + 16 * j;
+        const int t = tl + 16 * JS * j;
         if (lane < 16 && t < R && t < T && vt < o.n_vt) {
           const size_t idx = (size_t)t * o.n_vt + vt;
           o.pm1[idx] = p.m1; o.pi1[idx] = p.i1; o.pm2[idx] = p.m2; o.pi2[idx] = p.i2; o.ps[idx] = p.s;
           o.pt[idx] = p.t;
         }
       } else {
-        if (lane < 16) xch_slot()[wave_w][(wave_t * ST + j) * 16 + lane] = p;
+        if (lane < 16) xch_slot<NTOK>()[wave_w][(wave_t * ST + j) * 16 + lane] = p;
       }
     }
     if constexpr (!kOwn && WW > 1) {
-      Part(*xch)[256] = xch_slot();
+      Part(*xch)[NTOK] = xch_slot<NTOK>();
       __syncthreads();
       if (wave_w == 0) {
 #pragma unroll
         for (int j = 0; j < ST; ++j) {
-          const int t = tl + 16 * j;
+          const int t = tl + 16 * JS * j;
           if (lane < 16 && t < R && t < T) {
             Part p = xch[0][(wave_t * ST + j) * 16 + lane];
 #pragma unroll
@@ -337,7 +344,7 @@ struct EpiLm {
 // slice epilogue (EpiPartial: one float32 slice per split, no unit waits on another); the consumer
 // adds the slices in split order, so results are bitwise reproducible. nsplit > 1 is only used with
 // a slice epilogue.
-__device__ __attribute__((aligned(64))) uint4 g_zero_chunk[4];
+static __device__ __attribute__((aligned(64))) uint4 g_zero_chunk[4];
 
 // dma16_at with the LDS destination already wave-uniform (a scalar register)
 __device__ __forceinline__ void dma16_lds(const void* g, uint32_t lds_addr) {
@@ -504,226 +511,322 @@ gemm_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, 
   }
 }
 
-// Register-prefetch variant: global -> VGPR loads run PF stages ahead of the MFMAs (the data in
-// flight sits in registers, not in LDS), each stage is written into a double-buffered,
-// XOR-swizzled LDS tile just before it is needed. The compiler's vmcnt waits cover exactly the
-// stage being stored. Same unit order, split-K slices and epilogues as gemm_kernel.
-template <int BW, int BT, int PF, int WW, int WT, class Epi>
-__global__ void __launch_bounds__(WW * WT * 64)
-gemm_rp_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, int T, int K,
-               const int32_t* __restrict__ t_count, int nsplit, Epi epi) {
-  constexpr int NWAVE = WW * WT, NT = NWAVE * 64;
-  constexpr int TW = BW / WW, TT = BT / WT, SW = TW / 16, ST = TT / 16;
-  constexpr int CH = (BW + BT) * 8;   // 16-byte chunks per stage
-  constexpr int CPT = CH / NT;        // chunks per thread per stage
-  static_assert(TW % 16 == 0 && TT % 16 == 0 && CH % NT == 0, "tile shape");
-  extern __shared__ __attribute__((aligned(1024))) uint4 sm[];
-
-  const int nW = (Nw + BW - 1) / BW, nTt = (T + BT - 1) / BT;
-  const int tiles = nW * nTt, units = tiles * nsplit;
-  const int per = (units + 7) / 8;
-  const int L = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-  if (L >= units) return;
-  const int tile_t = L % nTt, rest = L / nTt;
-  const int tile_w = rest % nW, split = rest / nW;
-  const int tile = tile_w * nTt + tile_t;
-  const int w0 = tile_w * BW, t0 = tile_t * BT;
-  const int Tv = t_count ? min(T, *t_count) : T;
-  if (t0 >= Tv) return;
-  const int nk_all = (K + 63) / 64;
-  const int kper = (nk_all + nsplit - 1) / nsplit;
-  const int kb = min(nk_all, split * kper);
-  const int nk = min(nk_all, kb + kper) - kb;
-
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int wave_w = wid % WW, wave_t = wid / WW;
-
-  // chunk j of this thread: stage position pos = j * NT + tid; source pointer (null = zero chunk)
-  const bf16_t* src[CPT];
-  int lds_pos[CPT];
-  int kcol[CPT];
-#pragma unroll
-  for (int j = 0; j < CPT; ++j) {
-    const int pos = j * NT + tid;
-    const bool isw = pos < BW * 8;
-    const int p2 = isw ? pos : pos - BW * 8;
-    const int row = p2 >> 3, c = p2 & 7;
-    const int grow = (isw ? w0 : t0) + row;
-    src[j] = (grow < (isw ? Nw : Tv)) ? (isw ? W : X) + (size_t)grow * K + c * 8 : nullptr;
-    kcol[j] = c * 8;
-    lds_pos[j] = (isw ? 0 : BW * 8) + row * 8 + (c ^ (row & 7));
-  }
-  uint4 regs[PF][CPT];
-  auto gload = [&](int set, int kt) {
-    const int k0 = (kb + kt) * 64;
-#pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      regs[set][j] = (src[j] && k0 + kcol[j] < K) ? *reinterpret_cast<const uint4*>(src[j] + k0) : make_uint4(0, 0, 0, 0);
-  };
-  auto sstore = [&](int set, int buf) {
-    uint4* stage = sm + buf * CH;
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) stage[lds_pos[j]] = regs[set][j];
-  };
-
-  f32x4_t acc[SW][ST];
-#pragma unroll
-  for (int i = 0; i < SW; ++i)
-#pragma unroll
-    for (int j = 0; j < ST; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-#pragma unroll
-  for (int st = 0; st < PF; ++st)
-    if (st < nk) gload(st, st);
-  if (nk > 0) sstore(0, 0);
-  lds_barrier();
-  const int frow = lane & 15, fchunk = lane >> 4;
-  auto compute = [&](int buf) {
-    const uint4* stage = sm + buf * CH;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int c = 4 * ks + fchunk;
-      bf16x8_t a[SW], b[ST];
-#pragma unroll
-      for (int i = 0; i < SW; ++i) {
-        const int r = wave_w * TW + 16 * i + frow;
-        a[i] = __builtin_bit_cast(bf16x8_t, stage[r * 8 + (c ^ (r & 7))]);
-      }
-#pragma unroll
-      for (int j = 0; j < ST; ++j) {
-        const int r = wave_t * TT + 16 * j + frow;
-        b[j] = __builtin_bit_cast(bf16x8_t, stage[BW * 8 + r * 8 + (c ^ (r & 7))]);
-      }
-#pragma unroll
-      for (int i = 0; i < SW; ++i)
-#pragma unroll
-        for (int j = 0; j < ST; ++j) acc[i][j] = mfma16(a[i], b[j], acc[i][j]);
+// ---------------------------------------------------------------- the two-phase kernel
+// The large tiles. Eight waves, two per SIMD, as 2 (weight rows) x 4 (tokens); the two waves of a SIMD run
+// half a phase apart, so while one issues its MFMAs the other reads its fragments and issues the DMA:
+//
+//   interval        2j          2j+1         2j+2
+//   waves 0-3    read phase j   MFMA j     read j+1
+//   waves 4-7     MFMA j-1    read phase j   MFMA j       (a bare s_barrier between intervals)
+//
+// What bounds it: in gemm_kernel every wave of a workgroup reads fragments at the same time and then
+// multiplies at the same time, so the LDS port and the matrix pipe take turns (256 x 256 tiles at 3072 x 37888
+// x 3584: MFMA busy 57 % of the cycles at 2.09 GHz). Half a phase apart they overlap: 67 % at 1.92 GHz, where
+// the clock is what the power budget leaves. 662 -> 602 us (1386 TFLOP/s); 24576 x 1280 x 4096: 219 -> 199 us.
+//
+// A phase is one 64-deep K stage of all the wave's rows, or (two-stage rings, NPH = 2) half of the rows, so
+// that half a stage's weights can be refilled a phase earlier: the LDS ring is the limit on the bytes in
+// flight (64 KB per 256 x 256 stage). Order of the 1 KiB blocks of a stage, in LDS and for the DMA:
+// [weight rows of phase 0][tokens][weight rows of phase 1]; block q is copied by wave q mod 8.
+//   phase 0 of stage kt reads [.. tokens] and refills the previous stage's phase-1 rows (stage kt - 1 + S);
+//   phase 1 reads the phase-1 rows and refills [.. tokens] of the same buffer (stage kt + S).
+// A refill is safe: the rows were last read one phase earlier by the late waves (4-7), which wait for their
+// reads (lgkmcnt) before the barrier that starts the refilling interval. A stage is complete: each wave waits
+// for its own loads of the rows a phase needs (vmcnt; loads complete in order, and the same number per wave
+// is issued after them) before the barrier that starts the first interval reading them: the late waves in
+// their read interval, the early ones after their MFMAs, both in the interval just before.
+// Barriers per unit, with P = nk * NPH phases: early waves 1 + 2P; late waves 1 + 1 + 2P - 1 (they start one
+// interval later and skip the last). A K range without stages (nk = 0) has one barrier for both.
+//
+// Units as in gemm_kernel, but each XCD's run is walked in groups of `gw` weight tiles, all token tiles of
+// a group in turn (weight tile innermost), so the 32 workgroups of an XCD cover about gw x 8 tiles and share
+// both operands in its L2 (L2 misses limit the fill at thousands of tokens: at gw = 1, 27 % of the
+// requests of the case above miss). A workgroup issues the first stages of its next unit before the epilogue.
+// A partly filled token tile computes only the ceil(valid / 64) token fragments a wave needs: fragment j of
+// wave t is the tokens [64 j + 16 t, +16), so the valid ones spread over all waves.
+template <int IPW, int MAXN>
+__device__ __forceinline__ void wait_stages(int n) {  // all but this wave's newest n stages (IPW loads each) landed
+  if constexpr (MAXN > 0) {
+    if (n >= MAXN) {
+      wait_vmcnt<MAXN * IPW>();
+      return;
     }
-  };
-  // main loop, unrolled by PF so register-set indices are compile-time constants
-  for (int kt0 = 0; kt0 < nk; kt0 += PF) {
-#pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      const int kt = kt0 + u;
-      if (kt < nk) {
-        if (kt + PF < nk) gload(u, kt + PF);          // set u held stage kt, already in LDS
-        compute(kt & 1);
-        if (kt + 1 < nk) sstore((u + 1) % PF, (kt + 1) & 1);
-        lds_barrier();
-      }
-    }
+    wait_stages<IPW, MAXN - 1>(n);
+  } else {
+    wait_vmcnt<0>();
   }
-
-  if constexpr (Epi::kPartial) {
-    epi.template apply<SW, ST>(acc, w0 + wave_w * TW, t0 + wave_t * TT, lane, Nw, Tv, tile_w, split);
-    return;
-  }
-  epi.template apply<SW, ST>(acc, w0 + wave_w * TW, t0 + wave_t * TT, lane, Nw, Tv, tile_w, split);
+}
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+// One 1 KiB wave copy: 64 lanes x 16 bytes from a scalar base plus a per-lane byte offset.
+__device__ __forceinline__ void dma16_sv(const void* base, uint32_t voff, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base)
+               : "memory", "m0");
 }
 
-template <int BW, int BT, int PF, class Epi, int WW = 2, int WT = 2>
-static void run_rp(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const int32_t* t_count, int nsplit,
-                   const Epi& epi, hipStream_t s) {
-  const int tiles = ((Nw + BW - 1) / BW) * ((T + BT - 1) / BT);
-  const int units = tiles * nsplit;
-  if (units == 0) return;
-  const int grid = 8 * ((units + 7) / 8);
-  const size_t lds = (size_t)2 * (BW + BT) * 8 * 16;
-  auto kern = gemm_rp_kernel<BW, BT, PF, WW, WT, Epi>;
-  static std::atomic<uint32_t> lds_set{0};
-  ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_set);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(WW * WT * 64), lds, s, W, X, Nw, T, K, t_count, nsplit, epi);
+template <int BW, int BT, int S, class Epi>
+__global__ void __launch_bounds__(512)
+gemm_pp_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, int T, int K,
+               const int32_t* __restrict__ t_count, int nsplit, int gw, Epi epi) {
+  constexpr int WW = 2, WT = 4, NPH = S == 2 ? 2 : 1;
+  constexpr int TW = BW / WW, SW = TW / 16, ST = BT / 64, SWP = SW / NPH;
+  constexpr int NB = (BW + BT) / 8, IPW = NB / 8;       // 1 KiB blocks per stage, loads per wave and stage
+  constexpr uint32_t STAGE = (BW + BT) * 128;           // bytes per stage
+  constexpr int QX = BW / 8 / NPH, Q0 = QX + BT / 8;    // blocks [0, QX) weights, [QX, Q0) tokens, [Q0, NB) weights
+  static_assert(BW % 64 == 0 && BT % 64 == 0 && SW % NPH == 0 && S >= 2 && IPW * (S - 1) < 64, "tile shape");
+  extern __shared__ __attribute__((aligned(1024))) uint4 sm[];
+
+  const int Tv = t_count ? min(T, *t_count) : T;
+  const int nW = (Nw + BW - 1) / BW, nTt = (Tv + BT - 1) / BT;
+  const int units = nW * nsplit * nTt;
+  const int per = (units + 7) / 8;
+  const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3;
+  const int run_end = min(units, (xcd + 1) * per);
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wave_w = wid / WT, wave_t = wid % WT;
+  const bool late = wid >= 4;
+  const int frow = lane & 15, fchunk = lane >> 4;
+  const uint32_t lds0 = lds_addr_of(sm);
+  const int nk_all = K / 64, kper = (nk_all + nsplit - 1) / nsplit;
+  // lane i of a block copies chunk i % 8 of row i / 8 (rows of 8 chunks, XOR-swizzled as in gemm_kernel)
+  const uint32_t vchunk = (uint32_t)((lane & 7) ^ (lane >> 3)) * 16u;
+  // a fragment read: row frow, chunk 4 ks + fchunk
+  const uint32_t fo0 = (uint32_t)frow * 128u + (uint32_t)(fchunk ^ (frow & 7)) * 16u;
+  const uint32_t fo1 = (uint32_t)frow * 128u + (uint32_t)((fchunk + 4) ^ (frow & 7)) * 16u;
+
+  int L = xcd * per + (blockIdx.x >> 3);
+  if (L >= run_end) return;
+  const char *wbase, *xbase;
+  uint32_t voff[IPW];
+  int tile_w, split, w0, t0, nk, ste;
+  auto setup = [&](int u) {
+    split = u / (nW * nTt);
+    const int r = u - split * (nW * nTt);
+    const int g = r / (gw * nTt), rr = r - g * gw * nTt, gn = min(gw, nW - g * gw);
+    const int tile_t = rr / gn;
+    tile_w = g * gw + rr - tile_t * gn;
+    w0 = tile_w * BW;
+    t0 = tile_t * BT;
+    ste = min(ST, (Tv - t0 + 63) / 64);
+    const int kb = min(nk_all, split * kper);
+    nk = min(nk_all, kb + kper) - kb;
+    wbase = reinterpret_cast<const char*>(W + (size_t)w0 * K + kb * 64);
+    xbase = reinterpret_cast<const char*>(X + (size_t)t0 * K + kb * 64);
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      const int q = i * 8 + wid;
+      int row;  // rows outside the operand are clamped to the last valid row, as in gemm_kernel
+      if (q >= QX && q < Q0) {
+        row = min((q - QX) * 8 + (lane >> 3), Tv - t0 - 1);
+      } else {
+        constexpr int HR = SWP * 16;  // weight rows of one wave and phase; LDS order: phase, wave, row
+        const int slot = (q < QX ? q : q - BT / 8) * 8 + (lane >> 3);
+        const int ph = slot / (WW * HR), r2 = slot % (WW * HR);
+        row = min((r2 / HR) * TW + ph * HR + r2 % HR, Nw - w0 - 1);
+      }
+      voff[i] = (uint32_t)row * (uint32_t)K * 2u + vchunk;
+    }
+  };
+  auto copy = [&](int kt, int i) {
+    const int q = i * 8 + wid;
+    dma16_sv((q >= QX && q < Q0 ? xbase : wbase) + (size_t)kt * 128, voff[i],
+             lds0 + (uint32_t)(kt % S) * STAGE + (uint32_t)q * 1024u);
+  };
+  auto issue0 = [&](int kt) {  // phase-0 weights and tokens
+#pragma unroll
+    for (int i = 0; i < IPW; ++i)
+      if ((i + 1) * 8 <= Q0) copy(kt, i);
+      else if (i * 8 < Q0) {
+        if (wid < Q0 - i * 8) copy(kt, i);
+      }
+  };
+  auto issue1 = [&](int kt) {  // phase-1 weights (none with NPH = 1)
+#pragma unroll
+    for (int i = 0; i < IPW; ++i)
+      if (i * 8 >= Q0) copy(kt, i);
+      else if ((i + 1) * 8 > Q0) {
+        if (wid >= Q0 - i * 8) copy(kt, i);
+      }
+  };
+  auto prologue = [&]() {
+#pragma unroll
+    for (int st = 0; st < S; ++st)
+      if (st < nk) {
+        issue0(st);
+        issue1(st);
+      }
+  };
+
+  setup(L);
+  prologue();
+  while (true) {
+    f32x4_t acc[SW][ST];
+#pragma unroll
+    for (int i = 0; i < SW; ++i)
+#pragma unroll
+      for (int j = 0; j < ST; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    wait_stages<IPW, S - 1>(min(S, nk) - 1);
+    phase_barrier();
+    if (late && nk > 0) phase_barrier();
+    // instantiated twice: for a full token tile, and with a scalar branch around each fragment column
+    auto main_loop = [&](auto full_tile) {
+      constexpr bool kFull = decltype(full_tile)::value;
+      bf16x8_t fa[SWP][2], fb[ST][2];
+      for (int kt = 0; kt < nk; ++kt) {
+        const char* stage = reinterpret_cast<const char*>(sm) + (uint32_t)(kt % S) * STAGE;
+#pragma unroll
+        for (int ph = 0; ph < NPH; ++ph) {
+          const char* sa = stage + (ph ? Q0 : 0) * 1024 + wave_w * (SWP * 2048);
+          const char* sb = stage + QX * 1024 + wave_t * 2048;
+          if (ph == 0) {
+#pragma unroll
+            for (int j = 0; j < ST; ++j)
+              if (kFull || j == 0 || j < ste) {
+                fb[j][0] = *reinterpret_cast<const bf16x8_t*>(sb + j * 8192 + fo0);
+                fb[j][1] = *reinterpret_cast<const bf16x8_t*>(sb + j * 8192 + fo1);
+              }
+          }
+#pragma unroll
+          for (int i = 0; i < SWP; ++i) {
+            fa[i][0] = *reinterpret_cast<const bf16x8_t*>(sa + i * 2048 + fo0);
+            fa[i][1] = *reinterpret_cast<const bf16x8_t*>(sa + i * 2048 + fo1);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (NPH == 1 || ph == 1) {
+            const int nx = NPH == 1 ? kt - 1 + S : kt + S;
+            if ((NPH == 2 || kt > 0) && nx < nk) issue0(nx);
+          } else if (kt > 0 && kt - 1 + S < nk) {
+            issue1(kt - 1 + S);
+          }
+          // stages that may still fly while the next phase reads
+          auto landed = [&]() {
+            if (NPH == 1) wait_stages<IPW, S - 2>(min(S - 2, max(0, nk - 2 - kt)));
+            else wait_stages<IPW, S - 1>(min(S - 1, max(0, nk - 1 - ph - kt)));
+          };
+          if (late) landed();
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+          phase_barrier();
+          __builtin_amdgcn_s_setprio(1);
+          if constexpr (kFull) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+              for (int i = 0; i < SWP; ++i)
+#pragma unroll
+                for (int j = 0; j < ST; ++j)
+                  acc[ph * SWP + i][j] = mfma16(fa[i][ks], fb[j][ks], acc[ph * SWP + i][j]);
+          } else {
+#pragma unroll
+            for (int j = 0; j < ST - 1; ++j)
+              if (j == 0 || j < ste)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                  for (int i = 0; i < SWP; ++i)
+                    acc[ph * SWP + i][j] = mfma16(fa[i][ks], fb[j][ks], acc[ph * SWP + i][j]);
+          }
+          __builtin_amdgcn_s_setprio(0);
+          __builtin_amdgcn_sched_barrier(0);
+          if (!late) landed();
+          if (!(late && ph == NPH - 1 && kt == nk - 1)) phase_barrier();
+        }
+      }
+    };
+    if (ST == 1 || ste == ST) main_loop(std::true_type{});
+    else main_loop(std::false_type{});
+    const int ew = w0, et = t0, etile = tile_w, esplit = split;
+    L += stride;
+    const bool more = L < run_end;
+    if (more) {  // every wave's reads of the ring completed before the last barrier
+      setup(L);
+      prologue();
+    }
+    epi.template apply<SW, ST, WT>(acc, ew + wave_w * TW, et + wave_t * 16, lane, Nw, Tv, etile, esplit);
+    if (!more) break;
+  }
 }
 
 // ---------------------------------------------------------------- planning and dispatch
 struct TileCfg {
-  int bw, bt, kd, stages, ww, wt, rp;  // rp = 1: register-prefetch kernel, `stages` = prefetch depth
+  int bw, bt, kd, stages, ww, wt, pp;  // pp = 1: gemm_pp_kernel, 0: gemm_kernel
 };
-// Tile shapes (weight rows x tokens), K depth per stage, stages and wave grid, chosen among by
-// measurement on MI355X for the LLaDA / Dream shapes (the tuned table below). A K depth of 128
-// halves the number of stage handoffs, which is what limits the small-tile shapes; 8-16 waves per
-// workgroup keep the MFMA pipes busy while the LDS fragment reads of the next substep are in
-// flight.
 static const TileCfg kCfgs[] = {
-    {128, 128, 64, 2, 2, 4, 0},  {192, 192, 64, 3, 4, 2, 0},  {64, 64, 64, 4, 2, 2, 0},
-    {128, 256, 64, 3, 2, 4, 0},  {96, 192, 64, 3, 2, 2, 1},   {192, 192, 64, 2, 4, 2, 1},
-    {128, 128, 64, 3, 2, 4, 1},  {96, 192, 128, 2, 3, 4, 0},  {128, 96, 128, 2, 4, 2, 0},
-    {160, 128, 128, 2, 2, 4, 0}, {96, 192, 128, 2, 2, 4, 0},  {192, 192, 64, 3, 4, 4, 0},
-    {128, 128, 128, 2, 2, 4, 0}, {64, 192, 128, 2, 2, 4, 0},  {128, 192, 128, 2, 4, 4, 0},
-    {128, 128, 64, 3, 2, 4, 0},  {128, 256, 64, 3, 2, 8, 0},  {128, 192, 64, 3, 2, 4, 0},
-    {128, 256, 64, 2, 2, 8, 0},  {256, 256, 64, 2, 2, 4, 0},  {256, 192, 64, 2, 2, 4, 0},
-    {256, 128, 64, 3, 2, 2, 0},  {256, 256, 64, 2, 4, 2, 0},  {96, 192, 64, 4, 3, 4, 0},
-    {96, 192, 64, 3, 3, 4, 0},   {192, 96, 64, 3, 4, 3, 0},
+    {128, 128, 64, 2, 2, 4, 0}, {64, 64, 64, 4, 2, 2, 0},   {96, 192, 64, 3, 3, 4, 0},  {256, 256, 64, 2, 2, 4, 1},
+    {256, 192, 64, 2, 2, 4, 1}, {256, 128, 64, 3, 2, 4, 1}, {256, 64, 64, 4, 2, 4, 1},  {192, 256, 64, 2, 2, 4, 1},
+    {192, 192, 64, 3, 2, 4, 1}, {192, 128, 64, 4, 2, 4, 1}, {192, 64, 64, 4, 2, 4, 1},  {128, 256, 64, 3, 2, 4, 1},
+    {128, 192, 64, 4, 2, 4, 1}, {128, 128, 64, 4, 2, 4, 1}, {128, 64, 64, 3, 2, 4, 1},
 };
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 constexpr int kCUs = 256;
 constexpr size_t kLdsBytes = 160 * 1024;  // LDS per CU (gfx950)
 
-// Measured choices for the GEMM shapes of the LLaDA-8B / Dream-7B workloads (weight rows, tokens, K).
-struct TunedShape {
-  int nw, t, k, cfg, nsplit;
+static size_t cfg_lds(const TileCfg& c) { return (size_t)c.stages * (c.bw + c.bt) * (c.kd / 8) * 16; }
+
+// force_bw != 0 (the LM head): each wave owns a whole vocabulary tile of force_bw ids, or the tile is
+// force_bw weight rows split over exactly kLmWaves of the 8 waves, the layout the top-2 epilogue's cross-wave
+// merge is written for.
+static bool lm_ok(const TileCfg& c, int force_bw) {
+  if (!force_bw) return true;
+  if (c.bw / c.ww == force_bw) return true;
+  return c.bw == force_bw && c.ww == kLmWaves && c.ww * c.wt == 8 &&
+         cfg_lds(c) + sizeof(Part) * kLmWaves * c.bt <= kLdsBytes;
+}
+
+struct TileCost {
+  double a, b0, b1, m;
 };
-static const TunedShape kTuned[] = {
+static const TileCost kCost[2 * kNumCfgs] = {
 #include "gemm_tuned.inc"
 };
 
-static size_t cfg_lds(const TileCfg& c) {
-  return c.rp ? (size_t)2 * (c.bw + c.bt) * 8 * 16 : (size_t)c.stages * (c.bw + c.bt) * (c.kd / 8) * 16;
+// Estimated time (us) of a GEMM with configuration `ci` and n K splits: launch + rounds of resident workgroups,
+// each round a unit's fixed part plus its stages. A stage also takes no less than the weight rows that the
+// resident workgroups share out need from HBM (each distinct row once) at 5.4 TB/s, the rate the streaming
+// cases reach. Split-K slices are charged the read of the next RMSNorm (5 TB/s).
+static double plan_cost(int ci, bool lm, int n, int Nw, int T, int K) {
+  const TileCfg& c = kCfgs[ci];
+  const TileCost& k = kCost[(lm ? kNumCfgs : 0) + ci];
+  const int nW = (Nw + c.bw - 1) / c.bw, nT = (T + c.bt - 1) / c.bt;
+  const double units = (double)nW * nT * n;
+  const int nk = ((K + 63) / 64 + n - 1) / n;
+  const int per_cu = std::max(1, std::min<int>(c.pp ? 2 : 4, (int)(kLdsBytes / cfg_lds(c))));
+  const double slots = (double)kCUs * per_cu, active = std::min(units, slots);
+  const double rounds = std::ceil(units / slots);
+  // 64-token fragments computed: gemm_pp_kernel skips those past the last token
+  const double full = c.bt / 64.0, last = c.pp ? (double)((T - (nT - 1) * c.bt + 63) / 64) : full;
+  const double f = rounds > 1 ? (full * (nT - 1) + last) / nT : (nT > 1 ? full : last);
+  double stage = k.b0 + k.b1 * f;
+  if (active > kCUs) stage *= 1.0 + (active / kCUs - 1.0) * k.m;
+  const double hbm = std::max(1.0, active / nT) * c.bw * 128.0 / 5.4e6;
+  stage = std::pow(std::pow(stage, 4) + std::pow(hbm, 4), 0.25);
+  return 4.0 + rounds * (k.a + nk * stage) + (n > 1 ? n * (double)T * Nw * 4.0 / 5e6 : 0.0);
 }
 
-// Fallback estimate for shapes outside the table: saturated throughput of the configuration, or the
-// time of one workgroup when there are fewer workgroups than CUs.
-static double plan_cost(const TileCfg& c, int n, int Nw, int T, int K) {
-  const double tiles = (double)((Nw + c.bw - 1) / c.bw) * ((T + c.bt - 1) / c.bt);
-  const double units = tiles * n;
-  const int bpc = (int)(160 * 1024 / cfg_lds(c)) > 0 ? (int)(160 * 1024 / cfg_lds(c)) : 1;
-  const double sw = c.bw / 32.0, st = c.bt / 32.0;
-  const double eff = sw * st / (sw * st + 0.5 * (sw + st));
-  const double mac_rate = 2.5e15 / 2 / kCUs * 0.3;  // sustained MAC/s per CU
-  const double t_unit = (double)c.bw * c.bt * ((double)K / n) / eff / mac_rate;
-  const double slots = (double)kCUs * (bpc < 2 ? 1 : 2);
-  const double t_part = n > 1 ? 2.0 * (n - 1) * (double)T * Nw * 4 / 6e12 : 0.0;
-  return ceil(units / slots) * t_unit * (bpc < 2 ? 1.0 : 1.6) + t_part;
-}
-
-// force_bw != 0 (the LM head): the tile must be force_bw weight rows split over exactly
-// kLmWaves waves along W, the layout the top-2 epilogue's cross-wave merge is written for.
-static bool lm_ok(const TileCfg& c, int force_bw) {
-  if (!force_bw || c.rp) return !force_bw;
-  if (c.bw / c.ww == force_bw) return cfg_lds(c) <= kLdsBytes;  // each wave owns a vocabulary tile
-  return c.bw == force_bw && c.ww == kLmWaves && cfg_lds(c) + kLmEpiLds <= kLdsBytes;
-}
-
+#if !defined(DCL_GEMM_PART) || DCL_GEMM_PART == 1
 GemmPlan plan_gemm(int Nw, int T, int K, int force_bw, int max_split) {
   GemmPlan best{0, 1, 0};
-  bool found = false;
-  for (const TunedShape& ts : kTuned)
-    if (ts.nw == Nw && ts.t == T && ts.k == K && ts.nsplit <= max_split && lm_ok(kCfgs[ts.cfg], force_bw)) {
-      best.cfg = ts.cfg;
-      best.nsplit = ts.nsplit;
-      found = true;
-      break;
-    }
-  if (!found) {
-    double best_t = 1e30;
-    const int nk = (K + 63) / 64;
-    for (int ci = 0; ci < kNumCfgs; ++ci) {
-      if (!lm_ok(kCfgs[ci], force_bw)) continue;
-      for (int n = 1; n <= max_split; ++n) {
-        if (n > 1 && nk / n < 8) break;
-        const double t = plan_cost(kCfgs[ci], n, Nw, T, K);
-        if (t < best_t * 0.999) {
-          best_t = t;
-          best.cfg = ci;
-          best.nsplit = n;
-        }
+  double best_t = 1e30;
+  const bool lm = force_bw != 0;
+  const int nk = (K + 63) / 64;
+  for (int ci = 0; ci < kNumCfgs; ++ci) {
+    // K not a multiple of the stage depth: one tail-aware configuration (128 x 128, 64-deep stages, which also
+    // suits the LM head's split layout) serves every such shape, so the others carry no tail handling. It is
+    // the slower kernel everywhere else; 128 x 64 tiles pay only under the LM head (they halve the last round).
+    if ((K % kCfgs[ci].kd != 0) != (ci == 0)) continue;
+    if (ci == kNumCfgs - 1 && !lm) continue;
+    if (!lm_ok(kCfgs[ci], force_bw)) continue;
+    for (int n = 1; n <= max_split && (n == 1 || (n - 1) * ((nk + n - 1) / n) < nk); ++n) {
+      const double t = plan_cost(ci, lm, n, Nw, T, K);
+      if (t < best_t * 0.999) {
+        best_t = t;
+        best.cfg = ci;
+        best.nsplit = n;
       }
     }
   }
-  // K not a multiple of the plan's stage depth: one tail-aware configuration (128 x 128, 64-deep stages,
-  // which also suits the LM head's split layout) serves every such shape, none of the tuned model
-  // shapes, so the tuned kernels carry no tail handling; the register-prefetch kernel handles tails itself
-  if (!kCfgs[best.cfg].rp && K % kCfgs[best.cfg].kd != 0) best.cfg = 0;
   const TileCfg& c = kCfgs[best.cfg];
   best.tiles = ((Nw + c.bw - 1) / c.bw) * ((T + c.bt - 1) / c.bt);
   return best;
@@ -738,87 +841,115 @@ void gemm_cfg_shape(int cfg, int* shape) {
   shape[4] = c.ww;
   shape[5] = c.wt;
 }
+#endif
+
+// Per instantiation: the ring plus the epilogue's static LDS fit in a CU, and (once per device) the kernel's
+// dynamic-LDS limit is raised.
+static bool prepare_kernel(const void* kern, size_t lds, std::atomic<int>& fits, std::atomic<uint32_t>& lds_set) {
+  if (fits.load(std::memory_order_acquire) < 0) {  // -1 = not yet known
+    hipFuncAttributes at{};
+    fits.store(hipFuncGetAttributes(&at, kern) == hipSuccess && at.sharedSizeBytes + lds <= kLdsBytes,
+               std::memory_order_release);
+  }
+  if (!fits.load(std::memory_order_acquire)) return false;
+  ensure_dynamic_lds(kern, lds, lds_set);
+  return true;
+}
 
 template <int BW, int BT, int KD, int STAGES, int WW, int WT, class Epi, bool KTAIL = false>
-static void run_cfg(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const int32_t* t_count, int nsplit,
+static bool run_cfg(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const int32_t* t_count, int nsplit,
                     const Epi& epi, hipStream_t s) {
-  const int tiles = ((Nw + BW - 1) / BW) * ((T + BT - 1) / BT);
-  const int units = tiles * nsplit;
-  if (units == 0) return;
+  const int units = ((Nw + BW - 1) / BW) * ((T + BT - 1) / BT) * nsplit;
+  if (units == 0) return true;
   // One workgroup per unit; with a device-side row count the grid is capped (workgroups stride
   // over the units that turn out to be active) so inactive token tiles cost no dispatch.
   int grid = 8 * ((units + 7) / 8);
   if (t_count && grid > 8 * kCUs) grid = 8 * kCUs;
   const size_t lds = (size_t)STAGES * (BW + BT) * (KD / 8) * 16;
   auto kern = gemm_kernel<BW, BT, KD, STAGES, WW, WT, Epi, KTAIL>;
-  // per instantiation: the ring plus the epilogue's static LDS fit in a CU (-1 = not yet known)
   static std::atomic<int> fits{-1};
-  if (fits.load(std::memory_order_acquire) < 0) {
-    hipFuncAttributes at{};
-    fits.store(hipFuncGetAttributes(&at, reinterpret_cast<const void*>(kern)) == hipSuccess &&
-                   at.sharedSizeBytes + lds <= kLdsBytes,
-               std::memory_order_release);
-  }
-  // A ring that does not fit is never planned (plans respect kLdsBytes). Rather than a launch the runtime
-  // would reject, the smallest configuration runs; that one always fits and is launched even if the
-  // attribute query itself failed, so this never recurses.
-  constexpr bool kSmallest = BW == 128 && BT == 128 && KD == 64 && STAGES == 2 && WW == 2 && WT == 4;
-  if constexpr (!kSmallest) {
-    if (!fits.load(std::memory_order_acquire)) {
-      run_cfg<128, 128, 64, 2, 2, 4, Epi, KTAIL>(W, X, Nw, T, K, t_count, nsplit, epi, s);
-      return;
-    }
-  }
   static std::atomic<uint32_t> lds_set{0};
-  ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_set);
+  if (!prepare_kernel(reinterpret_cast<const void*>(kern), lds, fits, lds_set)) return false;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(WW * WT * 64), lds, s, W, X, Nw, T, K, t_count, nsplit, epi);
+  return true;
 }
 
-static_assert(kNumCfgs == 26, "run_plan dispatches every configuration of kCfgs");
+// Weight tiles walked together by an XCD (see gemm_pp_kernel): 4 x 8 tiles of the 32 workgroups.
+constexpr int kGroupW = 4;
+
+template <int BW, int BT, int S, class Epi>
+static bool run_pp(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const int32_t* t_count, int nsplit,
+                   const Epi& epi, hipStream_t s) {
+  const int units = ((Nw + BW - 1) / BW) * ((T + BT - 1) / BT) * nsplit;
+  if (units == 0) return true;
+  constexpr size_t lds = (size_t)S * (BW + BT) * 128;
+  constexpr int slots = kCUs * (2 * lds <= kLdsBytes ? 2 : 1);  // resident workgroups; they stride over the units
+  const int grid = std::min(8 * ((units + 7) / 8), slots);
+  auto kern = gemm_pp_kernel<BW, BT, S, Epi>;
+  static std::atomic<int> fits{-1};
+  static std::atomic<uint32_t> lds_set{0};
+  if (!prepare_kernel(reinterpret_cast<const void*>(kern), lds, fits, lds_set)) return false;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, s, W, X, Nw, T, K, t_count, nsplit, kGroupW, epi);
+  return true;
+}
+
+static_assert(kNumCfgs == 15, "run_plan dispatches every configuration of kCfgs");
+
+// Whether the epilogue has a kernel for configuration CI: the LM head runs only the layouts of lm_ok, the debug
+// logits (test support) one tile, and 128 x 64 tiles serve only the LM head.
+template <class Epi, int CI>
+constexpr bool has_cfg() {
+  if (Epi::kKind == kEpiLm) return (CI >= 3 && CI <= 6) || CI == 11 || CI == 13 || CI == 14;
+  if (Epi::kKind == kEpiDebug) return CI == 13;
+  return CI != 14;
+}
 
 template <class Epi>
 static void run_plan(const GemmPlan& p, const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const int32_t* t_count,
                      const Epi& epi, hipStream_t s) {
   const int n = p.nsplit;
-  if (!kCfgs[p.cfg].rp && K % kCfgs[p.cfg].kd != 0) {  // plan_gemm gives such shapes configuration 0
-    run_cfg<128, 128, 64, 2, 2, 4, Epi, true>(W, X, Nw, T, K, t_count, n, epi, s);
-    return;
+  bool ok = false;
+#define DCL_RING(CI, ...) \
+  case CI: if constexpr (has_cfg<Epi, CI>()) ok = run_cfg<__VA_ARGS__>(W, X, Nw, T, K, t_count, n, epi, s); break
+#define DCL_PP(CI, ...) \
+  case CI: if constexpr (has_cfg<Epi, CI>()) ok = run_pp<__VA_ARGS__>(W, X, Nw, T, K, t_count, n, epi, s); break
+  if (K % kCfgs[p.cfg].kd == 0) {
+    switch (p.cfg) {
+      DCL_RING(1, 64, 64, 64, 4, 2, 2);
+      DCL_RING(2, 96, 192, 64, 3, 3, 4);
+      DCL_PP(3, 256, 256, 2);
+      DCL_PP(4, 256, 192, 2);
+      DCL_PP(5, 256, 128, 3);
+      DCL_PP(6, 256, 64, 4);
+      DCL_PP(7, 192, 256, 2);
+      DCL_PP(8, 192, 192, 3);
+      DCL_PP(9, 192, 128, 4);
+      DCL_PP(10, 192, 64, 4);
+      DCL_PP(11, 128, 256, 3);
+      DCL_PP(12, 128, 192, 4);
+      DCL_PP(13, 128, 128, 4);
+      DCL_PP(14, 128, 64, 3);
+    }
   }
-  switch (p.cfg) {
-    case 0: run_cfg<128, 128, 64, 2, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 1: run_cfg<192, 192, 64, 3, 4, 2>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 2: run_cfg<64, 64, 64, 4, 2, 2>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 3: run_cfg<128, 256, 64, 3, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 4: run_rp<96, 192, 3, Epi, 2, 2>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 5: run_rp<192, 192, 2, Epi, 4, 2>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 6: run_rp<128, 128, 3, Epi, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 7: run_cfg<96, 192, 128, 2, 3, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 8: run_cfg<128, 96, 128, 2, 4, 2>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 9: run_cfg<160, 128, 128, 2, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 10: run_cfg<96, 192, 128, 2, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 11: run_cfg<192, 192, 64, 3, 4, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 12: run_cfg<128, 128, 128, 2, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 13: run_cfg<64, 192, 128, 2, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 14: run_cfg<128, 192, 128, 2, 4, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 15: run_cfg<128, 128, 64, 3, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 16: run_cfg<128, 256, 64, 3, 2, 8>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 17: run_cfg<128, 192, 64, 3, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 18: run_cfg<128, 256, 64, 2, 2, 8>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 19: run_cfg<256, 256, 64, 2, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 20: run_cfg<256, 192, 64, 2, 2, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 21: run_cfg<256, 128, 64, 3, 2, 2>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 22: run_cfg<256, 256, 64, 2, 4, 2>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 23: run_cfg<96, 192, 64, 4, 3, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    case 24: run_cfg<96, 192, 64, 3, 3, 4>(W, X, Nw, T, K, t_count, n, epi, s); break;
-    default: run_cfg<192, 96, 64, 3, 4, 3>(W, X, Nw, T, K, t_count, n, epi, s); break;
-  }
+#undef DCL_RING
+#undef DCL_PP
+  // Configuration 0 (K tails); also a ring that does not fit (never planned: plans respect kLdsBytes), rather
+  // than a launch the runtime would reject. The tail-aware kernel is correct for every shape and always fits.
+  if (!ok) run_cfg<128, 128, 64, 2, 2, 4, Epi, true>(W, X, Nw, T, K, t_count, n, epi, s);
 }
 
+// The wrappers below are compiled as three objects (DCL_GEMM_PART 1-3, in parallel), or all at once.
+#ifndef DCL_GEMM_PART
+#define DCL_GEMM_PART 0
+#endif
+#define DCL_PART(n) (DCL_GEMM_PART == 0 || DCL_GEMM_PART == n)
+
+#if DCL_PART(1)
 void gemm_qkv(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const QkvOut& o, hipStream_t s) {
-  const GemmPlan p = plan_gemm(Nw, T, K, 0, 1);
-  if (o.dh == 128) run_plan(p, W, X, Nw, T, K, nullptr, EpiQkv<128>{o}, s);
-  else run_plan(p, W, X, Nw, T, K, nullptr, EpiQkv<64>{o}, s);
+  run_plan(plan_gemm(Nw, T, K, 0, 1), W, X, Nw, T, K, nullptr, EpiQkv{o}, s);
 }
+#endif
+#if DCL_PART(2)
 int gemm_resid(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, float* r, float* P, hipStream_t s) {
   const GemmPlan p = plan_gemm(Nw, T, K, 0, P ? kMaxSplit : 1);
   if (p.nsplit > 1) {
@@ -828,15 +959,19 @@ int gemm_resid(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, float* r,
   run_plan(p, W, X, Nw, T, K, nullptr, EpiResid{r}, s);
   return 0;
 }
+#endif
+#if DCL_PART(3)
 void gemm_swiglu(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, bf16_t* a, hipStream_t s) {
   run_plan(plan_gemm(Nw, T, K, 0, 1), W, X, Nw, T, K, nullptr, EpiSwiglu{a}, s);
 }
 void gemm_store_f32(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, float* out, hipStream_t s) {
-  run_plan(plan_gemm(Nw, T, K, 0, 1), W, X, Nw, T, K, nullptr, EpiF32{out}, s);
+  const GemmPlan p{K % 64 ? 0 : 13, 1, 0};
+  run_plan(p, W, X, Nw, T, K, nullptr, EpiF32{out}, s);
 }
 void gemm_lmhead(const bf16_t* W, const bf16_t* X, int V, int T, int K, const LmOut& o, hipStream_t s) {
   static_assert(kLmTile == 128 && kLmWaves == 2, "the LM-head vocabulary tile is the GEMM's weight tile");
   run_plan(plan_gemm(V, T, K, kLmTile, 1), W, X, V, T, K, o.count, EpiLm<kLmTile, kLmWaves>{o}, s);
 }
+#endif
 
 }  // namespace dcl

@@ -1,0 +1,129 @@
+"""Every GEMM tile configuration at the edges of its tiles: token counts one past or short of a tile, partly
+filled fragment columns, weight rows that leave partial tiles, short K ranges and K splits, against float64.
+
+Layers: dcl_debug_layer without RoPE (the projections are then plain products), each stage fed the GPU's own
+input. A sum of K products in any order, every addition rounded, errs by at most (K + c) 2^-23 sum |terms|
+(2^-23: twice the round-to-nearest unit, so truncating accumulators are covered); a bfloat16 store adds half
+an ulp, at most 2^-8 of the value. Head: dcl_score_hidden on given rows, at the exact-input bar of the suite.
+"""
+import dataclasses
+
+import pytest
+
+import synth
+from helpers import CONF_TOL, LOGIT_TOL, TIE_GAP
+
+# (d_model, d_ffn, heads x 64, tokens): the plans of their four GEMMs cover every configuration (checked below)
+LAYERS = [(384, 6144, 4, 17), (384, 6144, 4, 129), (384, 6144, 4, 200), (384, 6144, 4, 385), (384, 6144, 4, 449),
+          (384, 6144, 4, 513), (384, 6144, 4, 700), (384, 6144, 4, 770), (384, 6144, 4, 1025), (384, 6144, 16, 1300),
+          (256, 3072, 4, 700), (1024, 3072, 16, 1025), (1024, 3072, 16, 600), (2048, 3072, 16, 1025),
+          (1152, 12288, 2, 497), (400, 208, 4, 131)]
+HEADS = [(1000, 256, 1), (5003, 256, 63), (40001, 128, 65), (40000, 128, 130), (40010, 128, 200), (20000, 256, 257),
+         (126464, 128, 33), (126464, 128, 64), (5003, 208, 131)]
+
+
+def _plans(dcl):
+    layer, head = set(), set()
+    for d, F, H, T in LAYERS:
+        hd = 64 * H
+        for nw, k, split in ((3 * hd, d, 1), (d, hd, 4), (2 * F, d, 1), (d, F, 4)):
+            layer.add(dcl.dcl_debug_gemm_plan(nw, T, k, False, split)["cfg"])
+    for V, d, n in HEADS:
+        head.add(dcl.dcl_debug_gemm_plan(V, n, d, True, 1)["cfg"])
+    return layer, head
+
+
+def test_shapes_cover_every_configuration():
+    import paper_2607_20467_amd as dcl
+    layer, head = _plans(dcl)
+    assert layer >= set(range(14)) - {6}, f"configurations {sorted(set(range(14)) - {6} - layer)} not covered"
+    assert head >= {0, 3, 4, 5, 6, 14}, f"head configurations covered: {sorted(head)}"
+
+
+def _geom(d, F, H, V=512):
+    return dataclasses.replace(synth.TINY, name="tiles", n_layers=1, d_model=d, n_heads=H, n_kv_heads=H, head_dim=64,
+                               d_ffn=F, vocab=V, mask_id=V - 1, weight_dtype="bf16")
+
+
+def _weights(g, gen):
+    import torch
+    out = []
+    for name, shape, kind in synth.tensor_specs(g):
+        if kind == "bias":
+            out.append(None)
+        elif kind == "gain":
+            out.append(torch.ones(shape, dtype=torch.bfloat16, device="cuda"))
+        else:
+            out.append((torch.randn(shape, generator=gen, device="cuda") * 0.05).to(torch.bfloat16))
+    return out
+
+
+def _check(name, got, want, bound, bf16):
+    tol = bound + (want.abs() * 2.0 ** -8 if bf16 else 0)
+    bad = ~((got.double() - want).abs() <= tol)          # NaN counts as bad
+    assert not bool(bad.any()), f"{name}: {int(bad.sum())} of {bad.numel()} elements outside the bound"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,F,H,T", LAYERS)
+def test_layer_tiles(d, F, H, T):
+    import torch
+    import paper_2607_20467_amd as dcl
+    print(f"case layer d {d} F {F} H {H} T {T}", flush=True)
+    g = _geom(d, F, H)
+    gen = torch.Generator(device="cuda").manual_seed(d + F + T)
+    w = _weights(g, gen)
+    run = dcl.Runner(g, w, max_positions=2048, rope_enabled=False)
+    hd, Sp = 64 * H, (T + 7) // 8 * 8
+    r = torch.randn((T, d), generator=gen, device="cuda")
+    i16, f32 = torch.int16, torch.float32
+    taps = {k: torch.full((n,), -1, dtype=t, device="cuda") for k, n, t in
+            (("u", T * d, i16), ("q", T * hd, i16), ("k", T * hd, i16), ("v", hd * Sp, i16), ("o", T * hd, i16),
+             ("r_mid", T * d, f32), ("u2", T * d, i16), ("a", T * F, i16), ("r_out", T * d, f32))}
+    ws, n = run.workspace(1, T)
+    dcl.dcl_debug_layer(run.model, 1, T, None, 0, r, taps, ws, n)
+    b = {k: (v.view(torch.bfloat16) if v.dtype == i16 else v).double() for k, v in taps.items()}
+    wq, wk, wv, _, _, _, wo, wg, wu, wd = (None if x is None else x.double() for x in w[1:11])
+
+    def proj(x, m, extra=2):
+        return x @ m.t(), (x.shape[1] + extra) * 2.0 ** -23 * (x.abs() @ m.abs().t())
+    u, o, u2, a = b["u"].view(T, d), b["o"].view(T, hd), b["u2"].view(T, d), b["a"].view(T, F)
+    for name, m in (("q", wq), ("k", wk)):
+        _check(name, b[name].view(H, T, 64).transpose(0, 1).reshape(T, hd), *proj(u, m), True)
+    v = b["v"].view(hd, Sp)
+    _check("v", v[:, :T].t(), *proj(u, wv), True)
+    assert bool((v[:, T:] == 0).all()), "v padding"
+    y, e = proj(o, wo, 6)
+    _check("r_mid", b["r_mid"].view(T, d), r.double() + y, e + (hd + 6) * 2.0 ** -23 * r.double().abs(), False)
+    (gt, eg), (up, eu) = proj(u2, wg), proj(u2, wu)
+    s = torch.nn.functional.silu(gt)
+    _check("a", a, s * up, 1.1 * eg * up.abs() + s.abs() * eu + eg * eu + (s * up).abs() * (gt.abs() + 8) * 2.0 ** -21,
+           True)
+    y, e = proj(a, wd, 6)
+    r_mid = b["r_mid"].view(T, d)
+    _check("r_out", b["r_out"].view(T, d), r_mid + y, e + (F + 6) * 2.0 ** -23 * r_mid.abs(), False)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("V,d,n", HEADS)
+def test_head_tiles(V, d, n):
+    import torch
+    import paper_2607_20467_amd as dcl
+    print(f"case head V {V} d {d} n {n}", flush=True)
+    g = _geom(d, 16, 1, V)
+    gen = torch.Generator(device="cuda").manual_seed(V + d + n)
+    w = _weights(g, gen)
+    run = dcl.Runner(g, w, max_positions=16)
+    hidden = torch.randn((n, d), generator=gen, device="cuda").to(torch.bfloat16)
+    st = run.score_hidden(hidden)
+    logits = hidden.double() @ w[-1].double().t()
+    top = logits.topk(2, -1)
+    lse = logits.logsumexp(-1)
+    clear = top.values[:, 0] - top.values[:, 1] > TIE_GAP
+    assert bool((st["top1"][clear].long() == top.indices[:, 0][clear]).all())
+    assert float((st["lse"].double() - lse).abs().max()) <= LOGIT_TOL
+    for key, i in (("conf", 0), ("p2", 1)):
+        assert float((st[key].double() - torch.exp(top.values[:, i] - lse)).abs().max()) <= CONF_TOL, key
+    p = torch.softmax(logits, -1)
+    H = lse - (p * logits).sum(-1)
+    assert float((st["entropy"].double() - H).abs().max()) <= LOGIT_TOL
