@@ -225,6 +225,131 @@ __device__ __forceinline__ Part part_merge(const Part& a, const Part& b) {
   return o;
 }
 
+// Value of lane ^ 16 and lane ^ 32 paired with the lane's own by the lane-swap instructions (no LDS round
+// trip): op gets both values, in an order that is the same in both lanes, so it must be symmetric.
+template <class Op>
+__device__ __forceinline__ float pair_lanes(float v, bool far, Op op) {
+  const int b = __builtin_bit_cast(int, v);
+  if (far) {
+    const auto p = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return op(__builtin_bit_cast(float, (int)p[0]), __builtin_bit_cast(float, (int)p[1]));
+  }
+  const auto p = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  return op(__builtin_bit_cast(float, (int)p[0]), __builtin_bit_cast(float, (int)p[1]));
+}
+
+// Statistics of one token fragment j over the wave's 16 * SW ids, every lane of a token's four ends with them:
+// a scan over the lane's values (in id order, so a strict > keeps the lowest id of equal values), a butterfly
+// over the four lanes of the token, then the sums relative to the wave's top-1 value. VALU-bound: about 7
+// operations a value for the top two with their ids and 8 for the sums (the exponential counts 4), against
+// about 28 with ties, the vocabulary's end and the left-out id tested per value (the general version below):
+// 126464 x 4096 at 32 / 256 rows 202 -> 183 / 266 -> 251 us, 152064 x 3584 at 1920 rows 1850 -> 1707 us. Returns false where a value is not finite enough for the short cuts
+// (NaN, infinities, fewer than two values above -inf); the general version then gives that fragment.
+template <int SW, int ST>
+__device__ __forceinline__ bool lm_fragment(const f32x4_t (&acc)[SW][ST], int j, int wq, Part& p) {
+  float m1 = fmaxf(acc[0][j][0], acc[0][j][1]), m2 = fminf(acc[0][j][0], acc[0][j][1]);
+  int n1 = acc[0][j][1] > acc[0][j][0] ? 1 : 0, n2 = 1 - n1;
+#pragma unroll
+  for (int n = 2; n < 4 * SW; ++n) {
+    const float v = acc[n >> 2][j][n & 3];
+    const int id = 16 * (n >> 2) + (n & 3);
+    const bool c1 = v > m1, c2 = v > m2;
+    n2 = c1 ? n1 : (c2 ? id : n2);
+    n1 = c1 ? id : n1;
+    m2 = __builtin_amdgcn_fmed3f(m1, m2, v);
+    m1 = fmaxf(m1, v);
+  }
+  int i1 = wq + n1, i2 = wq + n2;
+#pragma unroll
+  for (int far = 0; far < 2; ++far) {
+    // both halves of the swap: (x, y) are the two lanes' values, in the same order in both lanes
+    auto both = [&](int v, int& x, int& y) {
+      if (far) {
+        const auto q = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        x = (int)q[0];
+        y = (int)q[1];
+      } else {
+        const auto q = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        x = (int)q[0];
+        y = (int)q[1];
+      }
+    };
+    int ma, mb, sa, sb, ia, ib, ja, jb;
+    both(__builtin_bit_cast(int, m1), ma, mb);
+    both(__builtin_bit_cast(int, m2), sa, sb);
+    both(i1, ia, ib);
+    both(i2, ja, jb);
+    const float a1 = __builtin_bit_cast(float, ma), b1 = __builtin_bit_cast(float, mb);
+    const float a2 = __builtin_bit_cast(float, sa), b2 = __builtin_bit_cast(float, sb);
+    const bool first = better(a1, ia, b1, ib);
+    const float lose = first ? b1 : a1, sec = first ? a2 : b2;
+    const int ilose = first ? ib : ia, isec = first ? ja : jb;
+    const bool keep = better(sec, isec, lose, ilose);
+    m1 = first ? a1 : b1;
+    i1 = first ? ia : ib;
+    m2 = keep ? sec : lose;
+    i2 = keep ? isec : ilose;
+  }
+  float s = 0.f, t = 0.f;
+#pragma unroll
+  for (int n = 0; n < 4 * SW; ++n) {
+    const float d = acc[n >> 2][j][n & 3] - m1;
+    const float e = __expf(d);
+    s += e;
+    t += e * d;
+  }
+  auto add = [](float x, float y) { return x + y; };
+  s = pair_lanes(s, false, add);
+  s = pair_lanes(s, true, add);
+  t = pair_lanes(t, false, add);
+  t = pair_lanes(t, true, add);
+  p = Part{m1, m2, s, t, i1, i2};
+  const float chk = s + t;
+  return __builtin_amdgcn_ballot_w64(!(fabsf(chk) < INFINITY)) == 0;
+}
+// The same with every id tested: ids at or past Nw and the left-out id do not count.
+template <int SW, int ST>
+__device__ __forceinline__ void lm_fragment_general(const f32x4_t (&acc)[SW][ST], int j, int wq, int Nw, int exclude,
+                                                    Part& p) {
+  p = {-INFINITY, -INFINITY, 0.f, 0.f, INT_MAX, INT_MAX};
+#pragma unroll
+  for (int i = 0; i < SW; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int w = wq + 16 * i + r;
+      if (w < Nw && w != exclude) top2_push(p, acc[i][j][r], w);
+    }
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {
+    Part x;
+    x.m1 = __shfl_xor(p.m1, off, 64); x.m2 = __shfl_xor(p.m2, off, 64);
+    x.i1 = __shfl_xor(p.i1, off, 64); x.i2 = __shfl_xor(p.i2, off, 64);
+    x.s = 0.f;
+    x.t = 0.f;
+    Part y = part_merge(p, x);  // symmetric: ids differ, so argument order does not matter
+    p.m1 = y.m1; p.m2 = y.m2; p.i1 = y.i1; p.i2 = y.i2;
+  }
+  float s = 0.f, t = 0.f;
+#pragma unroll
+  for (int i = 0; i < SW; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int w = wq + 16 * i + r;
+      if (w < Nw && w != exclude) {
+        const float d = acc[i][j][r] - p.m1;
+        const float e = __expf(d);
+        s += e;
+        t += e * d;
+      }
+    }
+  s += __shfl_xor(s, 16, 64);
+  s += __shfl_xor(s, 32, 64);
+  t += __shfl_xor(t, 16, 64);
+  t += __shfl_xor(t, 32, 64);
+  p.s = s;
+  p.t = t;
+}
+
 // LM head: one partial per (token, vocabulary tile of kLmTile ids). Within a wave: per-lane scan of
 // its values, butterfly over the four lanes holding the same token, then a second pass for the sum
 // of exp(l - m1_wave). A wave whose weight rows span a whole vocabulary tile (16 * SW == kLmTile)
@@ -252,45 +377,15 @@ struct EpiLm {
     const int R = *o.count;
     const int vt = kOwn ? wb / kLmTile : tile_w;  // vocabulary tile of this wave's partial
     const int wq = wb + 4 * (lane >> 4), tl = tb + (lane & 15);
+    // the wave's ids all exist and none is left out
+    const bool inside = wb + 16 * SW <= Nw && (o.exclude < wb || o.exclude >= wb + 16 * SW);
 #pragma unroll
     for (int j = 0; j < ST; ++j) {
-      Part p = {-INFINITY, -INFINITY, 0.f, 0.f, INT_MAX, INT_MAX};
-#pragma unroll
-      for (int i = 0; i < SW; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int w = wq + 16 * i + r;
-          if (w < Nw && w != o.exclude) top2_push(p, acc[i][j][r], w);
-        }
-#pragma unroll
-      for (int off = 16; off <= 32; off <<= 1) {
-        Part x;
-        x.m1 = __shfl_xor(p.m1, off, 64); x.m2 = __shfl_xor(p.m2, off, 64);
-        x.i1 = __shfl_xor(p.i1, off, 64); x.i2 = __shfl_xor(p.i2, off, 64);
-        x.s = 0.f;
-        x.t = 0.f;
-        Part y = part_merge(p, x);  // symmetric: ids differ, so argument order does not matter
-        p.m1 = y.m1; p.m2 = y.m2; p.i1 = y.i1; p.i2 = y.i2;
-      }
-      float s = 0.f, t = 0.f;
-#pragma unroll
-      for (int i = 0; i < SW; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int w = wq + 16 * i + r;
-          if (w < Nw && w != o.exclude) {
-            const float d = acc[i][j][r] - p.m1;
-            const float e = __expf(d);
-            s += e;
-            t += e * d;
-          }
-        }
-      s += __shfl_xor(s, 16, 64);
-      s += __shfl_xor(s, 32, 64);
-      t += __shfl_xor(t, 16, 64);
-      t += __shfl_xor(t, 32, 64);
-      p.s = s;
-      p.t = t;
+      if (tb + 16 * JS * j >= T && (kOwn || WW == 1)) continue;  // no valid token in this fragment
+      Part p;
+      bool general = !inside;
+      if (inside) general = !lm_fragment<SW, ST>(acc, j, wq, p);
+      if (general) lm_fragment_general<SW, ST>(acc, j, wq, Nw, o.exclude, p);
       if constexpr (kOwn || WW == 1) {
         const int t = tl + 16 * JS * j;
         if (lane < 16 && t < R && t < T && vt < o.n_vt) {

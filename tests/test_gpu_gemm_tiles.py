@@ -127,3 +127,33 @@ def test_head_tiles(V, d, n):
     p = torch.softmax(logits, -1)
     H = lse - (p * logits).sum(-1)
     assert float((st["entropy"].double() - H).abs().max()) <= LOGIT_TOL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [20, 129])
+def test_head_ties_and_non_finite_logits(n):
+    """Equal logits rank by id wherever the equal ids sit (one lane, two lanes of a token, two vocabulary tiles),
+    a -inf logit takes no part, and a row with a NaN logit leaves the other rows alone."""
+    import torch
+    import paper_2607_20467_amd as dcl
+    V, d = 4000, 256
+    g = _geom(d, 16, 1, V)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    w = _weights(g, gen)
+    best = torch.full((d,), 0.25, dtype=torch.bfloat16, device="cuda")
+    groups = ([65, 66], [200, 204], [385, 401], [600, 2600], [1000, 1016, 3999])
+    hidden = (torch.rand((n, d), generator=gen, device="cuda") + 0.5).to(torch.bfloat16)
+    for ids in groups:
+        m = [x.clone() if x is not None else None for x in w]
+        m[-1][ids] = best
+        m[-1][17, 3] = -torch.inf                       # hidden[:, 3] > 0: logit -inf in every row
+        h = hidden.clone()
+        h[n - 1, 5] = torch.nan
+        st = dcl.Runner(g, m, max_positions=16).score_hidden(h)
+        assert st["top1"][:n - 1].tolist() == [ids[0]] * (n - 1)
+        assert st["top2"][:n - 1].tolist() == [ids[1]] * (n - 1)
+        logits = h[:n - 1].double() @ m[-1].double().t()
+        conf = torch.softmax(logits, -1)[:, ids[0]]
+        assert float((st["conf"][:n - 1].double() - conf).abs().max()) <= CONF_TOL
+        assert bool((st["conf"][:n - 1] == st["p2"][:n - 1]).all())
+        assert bool(st["conf"][n - 1].isnan())
