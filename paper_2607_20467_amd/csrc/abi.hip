@@ -762,7 +762,7 @@ dcl_status dcl_kv_append(dcl_model_t model, const int32_t* tokens, int32_t B, in
 }
 
 struct ScoreLayout {
-  size_t rows, count, pm1, pi1, pm2, pi2, ps, pt, total;
+  size_t pm1, pi1, pm2, pi2, ps, pt, total;
   int n_vt;
 };
 
@@ -775,8 +775,8 @@ static ScoreLayout score_layout(const dcl_config& c, int n) {
     return o;
   };
   L.n_vt = (c.vocab + kLmTile - 1) / kLmTile;
-  L.rows = take((size_t)n * 4);
-  L.count = take(4);
+  take((size_t)n * 4);  // a row map and its count once stood here; the size is what callers allocate
+  take(4);
   const size_t np = (size_t)n * L.n_vt * 4;
   L.pm1 = take(np);
   L.pi1 = take(np);
@@ -811,10 +811,7 @@ dcl_status dcl_score_hidden(dcl_model_t model, const void* hidden, int32_t n, dc
   const ScoreLayout L = score_layout(m->cfg, n);
   if (ws_bytes < L.total) return fail(DCL_E_WORKSPACE, "workspace %zu bytes < required %zu", ws_bytes, L.total);
   (void)hipGetLastError();
-  int32_t* rows = at<int32_t>(ws, L.rows);
-  int32_t* count = at<int32_t>(ws, L.count);
   hipStream_t s = stream;
-  launch_iota(rows, count, n, stream);
   LmOut lo;
   lo.pm1 = at<float>(ws, L.pm1);
   lo.pi1 = at<int32_t>(ws, L.pi1);
@@ -823,7 +820,7 @@ dcl_status dcl_score_hidden(dcl_model_t model, const void* hidden, int32_t n, dc
   lo.ps = at<float>(ws, L.ps);
   lo.pt = at<float>(ws, L.pt);
   lo.n_vt = L.n_vt;
-  lo.count = count;
+  lo.count = nullptr;  // every row
   {
     PROF(P_LM);
     gemm_lmhead(at<bf16_t>(m->wbuf, m->lay.lm), static_cast<const bf16_t*>(hidden), m->cfg.vocab, n, m->cfg.d_model,
@@ -831,7 +828,7 @@ dcl_status dcl_score_hidden(dcl_model_t model, const void* hidden, int32_t n, dc
   }
   {
     PROF(P_MERGE);
-    launch_merge(lo.pm1, lo.pi1, lo.pm2, lo.pi2, lo.ps, lo.pt, L.n_vt, rows, count, n, out, stream);
+    launch_merge(lo.pm1, lo.pi1, lo.pm2, lo.pi2, lo.ps, lo.pt, L.n_vt, nullptr, nullptr, n, out, stream);
   }
   return hip_check(hipGetLastError(), "score_hidden launch");
 }

@@ -93,6 +93,7 @@ void launch_rmsnorm(float* r, const float* g, bf16_t* u, int T, int d, float eps
                     const int32_t* count, const float* P, int nP, hipStream_t s);
 void launch_compact(const int32_t* tokens, const int32_t* p, int B, int S, int gen_end, int mask_id,
                     int score_all, int32_t* rows, int32_t* count, dcl_row_stats st, hipStream_t s);
+// rows null: row j's statistics go to row j; count null: max_rows rows
 void launch_merge(const float* pm1, const int32_t* pi1, const float* pm2, const int32_t* pi2,
                   const float* ps, const float* pt, int n_vt, const int32_t* rows, const int32_t* count,
                   int max_rows, dcl_row_stats st, hipStream_t s);
@@ -122,7 +123,7 @@ struct LmOut {
   float* pt;  // sum exp(l - m1) * (l - m1) per partial (entropy), relative like ps
   int32_t *pi1, *pi2;
   int n_vt;
-  const int32_t* count;  // number of valid X rows (device)
+  const int32_t* count;  // number of valid X rows (device), null: all T
   int exclude = -1;      // vocabulary id left out of the reduction (mask suppression), -1: none
 };
 // Tile shape / split-K choice for one GEMM shape (host).

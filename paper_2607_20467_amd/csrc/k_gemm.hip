@@ -470,7 +470,7 @@ struct EpiLm {
     // the wave grids of gemm_kernel (JS = 1) and gemm_pp_kernel (token fragments JS apart)
     const int wave_w = JS == 1 ? wid % WW : wid / JS, wave_t = JS == 1 ? wid / WW : wid % JS;
     constexpr int NTOK = ST * 16 * (8 / WW);  // tokens of the workgroup tile (8 waves)
-    const int R = *o.count;
+    const int R = o.count ? *o.count : T;
     const int vt = kOwn ? wb / kLmTile : tile_w;  // vocabulary tile of this wave's partial
     const int wq = wb + 4 * (lane >> 4), tl = tb + (lane & 15);
     // the wave's ids all exist and none is left out
