@@ -548,6 +548,19 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
+template <int IPW, int MAXN>
+__device__ __forceinline__ void wait_stages(int n) {  // all but this wave's newest n stages (IPW loads each) landed
+  if constexpr (MAXN > 0) {
+    if (n >= MAXN) {
+      wait_vmcnt<MAXN * IPW>();
+      return;
+    }
+    wait_stages<IPW, MAXN - 1>(n);
+  } else {
+    wait_vmcnt<0>();
+  }
+}
+
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 template <int BW, int BT, int KD, int STAGES, int WW, int WT, class Epi, bool KTAIL>
@@ -650,12 +663,7 @@ gemm_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, 
 #pragma unroll
     for (int st = 0; st < STAGES; ++st)
       if (st < nk) issue(st);
-    {  // stage 0 landed; stages 1 .. min(nk, STAGES) - 1 may still fly
-      const int pend = min(STAGES - 1, nk - 1);
-      if (STAGES >= 3 && pend >= 2) wait_vmcnt<(STAGES >= 3 ? 2 : 0) * IPW>();
-      else if (pend >= 1) wait_vmcnt<IPW>();
-      else wait_vmcnt<0>();
-    }
+    wait_stages<IPW, STAGES - 1>(min(STAGES, nk) - 1);  // stage 0 landed
     lds_barrier();
     bf16x8_t fa[2][SW], fb[2][ST];
     if (nk > 0) frag(0, 0, fa[0], fb[0]);
@@ -667,10 +675,7 @@ gemm_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, 
         } else {
           // stage kt + 1 landed (stages kt + 2 .. min(nk - 1, kt + STAGES - 1) may still fly);
           // after the barrier every wave holds stage kt in registers, so its buffer is refilled
-          const int pend = min(STAGES - 2, nk - 2 - kt);
-          if (STAGES >= 4 && pend >= 2) wait_vmcnt<(STAGES >= 4 ? 2 : 0) * IPW>();
-          else if (STAGES >= 3 && pend >= 1) wait_vmcnt<(STAGES >= 3 ? 1 : 0) * IPW>();
-          else wait_vmcnt<0>();
+          wait_stages<IPW, STAGES - 2>(min(STAGES - 2, nk - 2 - kt));
           lds_barrier();
           if constexpr (STAGES >= 3) {
             // the next stage's first fragments go out first, and the refill is issued between two
@@ -735,18 +740,6 @@ gemm_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, 
 // requests of the case above miss). A workgroup issues the first stages of its next unit before the epilogue.
 // A partly filled token tile computes only the ceil(valid / 64) token fragments a wave needs: fragment j of
 // wave t is the tokens [64 j + 16 t, +16), so the valid ones spread over all waves.
-template <int IPW, int MAXN>
-__device__ __forceinline__ void wait_stages(int n) {  // all but this wave's newest n stages (IPW loads each) landed
-  if constexpr (MAXN > 0) {
-    if (n >= MAXN) {
-      wait_vmcnt<MAXN * IPW>();
-      return;
-    }
-    wait_stages<IPW, MAXN - 1>(n);
-  } else {
-    wait_vmcnt<0>();
-  }
-}
 __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_barrier" ::: "memory");
@@ -949,7 +942,10 @@ static const TileCfg kCfgs[] = {
     {256, 192, 64, 2, 2, 4, 1}, {256, 128, 64, 3, 2, 4, 1}, {256, 64, 64, 4, 2, 4, 1},  {192, 256, 64, 2, 2, 4, 1},
     {192, 192, 64, 3, 2, 4, 1}, {192, 128, 64, 4, 2, 4, 1}, {192, 64, 64, 4, 2, 4, 1},  {128, 256, 64, 3, 2, 4, 1},
     {128, 192, 64, 4, 2, 4, 1}, {128, 128, 64, 4, 2, 4, 1}, {128, 64, 64, 3, 2, 4, 1},
+    // one token tile of weights streamed (stream_cfg)
+    {32, 32, 128, 4, 2, 2, 0},  {32, 64, 128, 6, 1, 4, 0},  {48, 64, 128, 5, 1, 4, 0},  {96, 64, 128, 3, 2, 2, 0},
 };
+constexpr int kModelCfgs = 15;  // the first ones: those that the cost model chooses from
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
 constexpr int kCUs = 256;
 constexpr size_t kLdsBytes = 160 * 1024;  // LDS per CU (gfx950)
@@ -969,7 +965,7 @@ static bool lm_ok(const TileCfg& c, int force_bw) {
 struct TileCost {
   double a, b0, b1, m;
 };
-static const TileCost kCost[2 * kNumCfgs] = {
+static const TileCost kCost[2 * kModelCfgs] = {
 #include "gemm_tuned.inc"
 };
 
@@ -979,7 +975,7 @@ static const TileCost kCost[2 * kNumCfgs] = {
 // cases reach. Split-K slices are charged the read of the next RMSNorm (5 TB/s).
 static double plan_cost(int ci, bool lm, int n, int Nw, int T, int K) {
   const TileCfg& c = kCfgs[ci];
-  const TileCost& k = kCost[(lm ? kNumCfgs : 0) + ci];
+  const TileCost& k = kCost[(lm ? kModelCfgs : 0) + ci];
   const int nW = (Nw + c.bw - 1) / c.bw, nT = (T + c.bt - 1) / c.bt;
   const double units = (double)nW * nT * n;
   const int nk = ((K + 63) / 64 + n - 1) / n;
@@ -997,17 +993,35 @@ static double plan_cost(int ci, bool lm, int n, int Nw, int T, int K) {
 }
 
 #if !defined(DCL_GEMM_PART) || DCL_GEMM_PART == 1
+// At most 64 tokens without a K split: the time is that of streaming the weights, and what decides it is how evenly
+// the CUs share them and how much each has in flight, so the smallest tile whose units fit one round of the CUs is
+// taken, with 128-deep stages (256 contiguous bytes of each weight row per load) filling the LDS. Against the
+// 64 x 64 tiles with 64-deep stages that the cost model picks (weights from HBM, us):
+//   64 tokens: 12288 x 4096 26.4 -> 24.3 (48 rows: 256 units, 64 rows: 192), 24576 x 4096 46.7 -> 43.0 (96 rows),
+//              4608 x 3584 20.0 -> 15.4 (32 rows); the wider tile loses in each (33.5 and 30.4 for 12288 with 32 and 96 rows)
+//   24 tokens, 32 x 32 tiles (their activations are half the loads): 24.4 -> 23.1, 41.3 -> 36.7, 17.7 -> 11.2
+// More weight rows than 96 x 256 (37888 x 3584 at 24 tokens: 192 x 64 tiles 48.5, 32 x 32 tiles 50.5), and residual
+// GEMMs (four K slices already give 64 x 64 tiles a unit per CU): the cost model.
+static int stream_cfg(int Nw, int T, int K) {
+  if (T > 64 || K % 128 != 0) return -1;
+  for (int ci = 16; ci <= 18; ++ci)
+    if (Nw <= kCfgs[ci].bw * kCUs) return T <= 32 ? 15 : ci;
+  return -1;
+}
+
 GemmPlan plan_gemm(int Nw, int T, int K, int force_bw, int max_split) {
   GemmPlan best{0, 1, 0};
   double best_t = 1e30;
   const bool lm = force_bw != 0;
   const int nk = (K + 63) / 64;
-  for (int ci = 0; ci < kNumCfgs; ++ci) {
+  const int sc = lm || max_split > 1 ? -1 : stream_cfg(Nw, T, K);
+  if (sc >= 0) best.cfg = sc;
+  for (int ci = 0; sc < 0 && ci < kModelCfgs; ++ci) {
     // K not a multiple of the stage depth: one tail-aware configuration (128 x 128, 64-deep stages, which also
     // suits the LM head's split layout) serves every such shape, so the others carry no tail handling. It is
     // the slower kernel everywhere else; 128 x 64 tiles pay only under the LM head (they halve the last round).
     if ((K % kCfgs[ci].kd != 0) != (ci == 0)) continue;
-    if (ci == kNumCfgs - 1 && !lm) continue;
+    if (ci == kModelCfgs - 1 && !lm) continue;
     if (!lm_ok(kCfgs[ci], force_bw)) continue;
     for (int n = 1; n <= max_split && (n == 1 || (n - 1) * ((nk + n - 1) / n) < nk); ++n) {
       const double t = plan_cost(ci, lm, n, Nw, T, K);
@@ -1084,7 +1098,7 @@ static bool run_pp(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const
   return true;
 }
 
-static_assert(kNumCfgs == 15, "run_plan dispatches every configuration of kCfgs");
+static_assert(kNumCfgs == 19, "run_plan dispatches every configuration of kCfgs");
 
 // Whether the epilogue has a kernel for configuration CI: the LM head runs only the layouts of lm_ok, the debug
 // logits (test support) one tile, and 128 x 64 tiles serve only the LM head.
@@ -1120,6 +1134,10 @@ static void run_plan(const GemmPlan& p, const bf16_t* W, const bf16_t* X, int Nw
       DCL_PP(12, 128, 192, 4);
       DCL_PP(13, 128, 128, 4);
       DCL_PP(14, 128, 64, 3);
+      DCL_RING(15, 32, 32, 128, 4, 2, 2);
+      DCL_RING(16, 32, 64, 128, 6, 1, 4);
+      DCL_RING(17, 48, 64, 128, 5, 1, 4);
+      DCL_RING(18, 96, 64, 128, 3, 2, 2);
     }
   }
 #undef DCL_RING

@@ -17,7 +17,9 @@ from helpers import CONF_TOL, LOGIT_TOL, TIE_GAP
 LAYERS = [(384, 6144, 4, 17), (384, 6144, 4, 129), (384, 6144, 4, 200), (384, 6144, 4, 385), (384, 6144, 4, 449),
           (384, 6144, 4, 513), (384, 6144, 4, 700), (384, 6144, 4, 770), (384, 6144, 4, 1025), (384, 6144, 16, 1300),
           (256, 3072, 4, 700), (1024, 3072, 16, 1025), (1024, 3072, 16, 600), (2048, 3072, 16, 1025),
-          (1152, 12288, 2, 497), (400, 208, 4, 131)]
+          (1152, 12288, 2, 497), (400, 208, 4, 131),
+          # one token tile (32 x 32 tiles; 32, 48 and 96 rows x 64 tokens): remainders of rows and tokens, short K
+          (128, 6144, 4, 33), (128, 4160, 4, 63), (128, 8000, 4, 64), (256, 2000, 4, 31), (1408, 304, 12, 1)]
 HEADS = [(1000, 256, 1), (5003, 256, 63), (40001, 128, 65), (40000, 128, 130), (40010, 128, 200), (20000, 256, 257),
          (126464, 128, 33), (126464, 128, 64), (5003, 208, 131)]
 
@@ -36,7 +38,8 @@ def _plans(dcl):
 def test_shapes_cover_every_configuration():
     import paper_2607_20467_amd as dcl
     layer, head = _plans(dcl)
-    assert layer >= set(range(14)) - {6}, f"configurations {sorted(set(range(14)) - {6} - layer)} not covered"
+    want = set(range(19)) - {6, 14}
+    assert layer >= want, f"configurations {sorted(want - layer)} not covered"
     assert head >= {0, 3, 4, 5, 6, 14}, f"head configurations covered: {sorted(head)}"
 
 
