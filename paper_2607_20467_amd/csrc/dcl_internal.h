@@ -52,6 +52,11 @@ __device__ __forceinline__ void dma16_at(const void* g, uint32_t lds_addr) {
 __device__ __forceinline__ uint32_t lds_addr_of(const void* lds) {
   return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds);
 }
+// One 1 KiB wave copy: 64 lanes x 16 bytes from a scalar base plus a per-lane byte offset.
+__device__ __forceinline__ void dma16_sv(const void* base, uint32_t voff, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base)
+               : "memory", "m0");
+}
 __device__ __forceinline__ void dma16(const void* g, const void* lds) { dma16_at(g, lds_addr_of(lds)); }
 
 // Packed-weight layout (byte offsets into the caller's weight buffer).

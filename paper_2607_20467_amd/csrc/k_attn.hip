@@ -41,6 +41,13 @@ __device__ __forceinline__ float xor_lanes32(float v, Op op) {
   return op(__builtin_bit_cast(float, (int)p[0]), __builtin_bit_cast(float, (int)p[1]));
 }
 
+// A wave-uniform address that the compiler computed in vector registers, in scalar ones.
+__device__ __forceinline__ const bf16_t* uniform_ptr(const bf16_t* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const bf16_t*>(((uint64_t)hi << 32) | lo);
+}
+
 template <int N>
 __device__ __forceinline__ void attn_wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
@@ -66,27 +73,32 @@ __device__ __forceinline__ void attn_wait_stages(int newer) {
 // chunks, bank-conflict free; the V^T fragments are then assembled by a lane-row swap (below).
 // Chunks past the last key repeat real data (see below).
 //
-// Key groups: the NQ * KG waves of a workgroup are NQ query waves (16 queries each) times KG key
+// What bounds it: per 16 queries x 32 keys (head_dim 128) a wave needs 512 matrix-pipe cycles (8 MFMAs for the
+// scores, 24 for the three-part P V), about as many VALU cycles, and 16 KB of fragments through the LDS port
+// (128 cycles, for four SIMDs again 512). So a wave takes QF x 16 queries: with QF = 2 each K and V^T fragment
+// (and the lane-row swap of V^T) serves both.
+//
+// Key groups: the NQ * KG waves of a workgroup are NQ query waves (16 QF queries each) times KG key
 // groups. Step t of the ring holds the KG key tiles t*KG .. t*KG + KG - 1; key group g works on
 // tile t*KG + g, so each wave's serial chain (scores -> softmax -> P V) covers 1/KG of the keys
 // and KG times as many waves hide each other's latencies. At the end the groups' running
 // (max, sum, unnormalised output) are combined through LDS in group order, which keeps the result
 // independent of timing.
-template <int NQ, int KG, int KT, int DH, int STAGES>
-__global__ void __launch_bounds__(NQ * KG * 64) attn_kernel(AttnArgs a) {
-  constexpr int BQ = 16 * NQ, NWAVE = NQ * KG;
+template <int NQ, int QF, int KG, int KT, int DH, int STAGES>
+__global__ void __launch_bounds__(NQ * KG * 64, 2) attn_kernel(AttnArgs a) {
+  constexpr int BQ = 16 * NQ * QF, NWAVE = NQ * KG;
   constexpr int KC = DH / 8;           // chunks per K row
   constexpr int VC = KT / 8;           // chunks per V^T row
   constexpr int KCH = KT * KC;         // K chunks per tile
   constexpr int VCH = DH * VC;         // V^T chunks per tile
   constexpr int TCH = KCH + VCH;       // chunks per tile
   constexpr int SCH = KG * TCH;        // chunks per ring step
-  constexpr int IPW = SCH / 64 / NWAVE;  // load instructions per wave per ring step
-  static_assert((KT == 32 || KT == 64) && SCH % (64 * NWAVE) == 0 && KCH % 64 == 0 && VCH % 64 == 0 &&
-                    STAGES >= 2 && IPW * (STAGES - 2) < 64 && NWAVE <= 16,
+  constexpr int KI = KCH / 64 / NWAVE, TI = TCH / 64 / NWAVE;  // K / all load instructions per wave and key tile
+  constexpr int IPW = KG * TI;         // load instructions per wave per ring step
+  static_assert((KT == 32 || KT == 64) && (KCH / 64) % NWAVE == 0 && (VCH / 64) % NWAVE == 0 && STAGES >= 2 &&
+                    IPW * (STAGES - 2) < 64 && NWAVE <= 16,
                 "stage shape");
-  static_assert(KG == 1 || (size_t)(KG - 1) * NQ * (DH / 16) * 64 * 16 + (size_t)(KG - 1) * NQ * 64 * 8 <=
-                                (size_t)STAGES * SCH * 16,
+  static_assert(KG == 1 || (size_t)(KG - 1) * NQ * QF * ((DH / 16) * 64 * 16 + 64 * 8) <= (size_t)STAGES * SCH * 16,
                 "the group merge reuses the ring");
   extern __shared__ __attribute__((aligned(1024))) uint4 sm[];
 
@@ -97,23 +109,26 @@ __global__ void __launch_bounds__(NQ * KG * 64) attn_kernel(AttnArgs a) {
   const int units = nqt * a.H * a.B, per = (units + 7) / 8;
   const int L = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
   if (L >= units) return;
-  const int qt = L % nqt, h = (L / nqt) % a.H, b = L / (nqt * a.H);
-  const int g = h / (a.H / a.Hkv);
+  // in scalar registers: the quotients come from vector arithmetic, the loads below want scalar bases
+  const int bh = __builtin_amdgcn_readfirstlane(L / nqt), b = __builtin_amdgcn_readfirstlane(bh / a.H);
+  const int qt = L - bh * nqt, h = bh - b * a.H, g = __builtin_amdgcn_readfirstlane(h / (a.H / a.Hkv));
   const int tid = threadIdx.x, lane = tid & 63, wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qw = wid % NQ, kg = wid / NQ;
   const int lq = lane & 15, lg = lane >> 4;
   const int S = a.S, P = a.P, Sk = a.Sk ? a.Sk : a.S, nkeys = P + Sk;  // S queries; P cached + Sk fresh keys
-  const int qrow = qt * BQ + qw * 16 + lq;
+  const int q0 = qt * BQ + qw * (16 * QF);  // first query of the wave
   const int ntiles = (nkeys + KT - 1) / KT;
   const int nsteps = (ntiles + KG - 1) / KG;
 
-  bf16x8_t qf[DH / 32];
-  {
+  bf16x8_t qf[QF][DH / 32];
+#pragma unroll
+  for (int f = 0; f < QF; ++f) {
+    const int qrow = q0 + 16 * f + lq;
     const bf16_t* qp = a.q + (((size_t)b * a.H + h) * S + (qrow < S ? qrow : 0)) * DH + 8 * lg;
 #pragma unroll
     for (int ks = 0; ks < DH / 32; ++ks) {
       uint4 v = qrow < S ? *reinterpret_cast<const uint4*>(qp + 32 * ks) : make_uint4(0, 0, 0, 0);
-      qf[ks] = __builtin_bit_cast(bf16x8_t, v);
+      qf[f][ks] = __builtin_bit_cast(bf16x8_t, v);
     }
   }
   const size_t kvh = (size_t)b * a.Hkv + g;
@@ -122,173 +137,195 @@ __global__ void __launch_bounds__(NQ * KG * 64) attn_kernel(AttnArgs a) {
   const bf16_t* vc = a.vc ? a.vc + kvh * DH * a.Pc : nullptr;
   const bf16_t* vf = a.vt + kvh * DH * a.Sp;
 
-  f32x4_t o[DH / 16];
+  f32x4_t o[QF][DH / 16];
 #pragma unroll
-  for (int dt = 0; dt < DH / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int f = 0; f < QF; ++f)
+#pragma unroll
+    for (int dt = 0; dt < DH / 16; ++dt) o[f][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   // per query: reference point m (log2 units, scaled; within 2^8 of the running maximum, see the
-  // lazy rescaling below) and the sum l of exp2(score - m)
-  float m = -INFINITY, l = 0.f;
+  // lazy rescaling below), the same in the query's four lanes, and the sum l of exp2(score - m) over
+  // this lane's keys (the four lanes' sums are added at the end)
+  float m[QF], l[QF];
+#pragma unroll
+  for (int f = 0; f < QF; ++f) {
+    m[f] = -INFINITY;
+    l[f] = 0.f;
+  }
   const float scale = a.scale_log2;
 
-  // DMA assignment: instruction i of wave w fills the 64-chunk block b = i * NWAVE + w of a ring
-  // step (block sizes are multiples of NWAVE, so the key group and the K / V^T role of instruction i
-  // are compile-time). Per ring step only the tile origin k0 changes: a chunk at key j < P comes
-  // from the cache, j < P + Sk from the fresh keys/values. A chunk past the last key re-reads the
-  // last key's (or last 8-key chunk's) data: those keys score -inf, so their probability is
-  // exactly 0 against finite values, and the address stays branch-free.
-  static_assert((KCH / 64) % NWAVE == 0 && (VCH / 64) % NWAVE == 0, "DMA blocks per wave");
-  constexpr int TB = TCH / 64;  // 64-chunk blocks per key tile
-  int jrel[IPW], offc[IPW];
-  const bf16_t* fsrc[IPW];  // fresh-key source for the tile origin k0 = P
+  // DMA assignment: load i of wave w fills the 64-chunk block i * NWAVE + w of a key tile (block sizes are
+  // multiples of NWAVE, so the K / V^T role of load i is compile-time). A tile that lies whole in the cache
+  // or whole in the fresh keys is a scalar base plus a per-lane offset that never changes: no vector
+  // arithmetic per load. Any other tile takes each chunk from the cache (key j < P) or the fresh keys / values
+  // by itself. A chunk past the last key re-reads the last key's (or last 8-key chunk's) data: those keys
+  // score -inf, so their probability is exactly 0 against finite values.
+  int key[TI];             // key of the chunk within the tile (V^T: first of its 8)
+  uint32_t voff[TI];       // byte offset from the tile's base: fresh operands
+  uint32_t coff[TI];       // the same in the cache (V^T rows of pitch Pc)
 #pragma unroll
-  for (int i = 0; i < IPW; ++i) {
-    const int bb = (i * NWAVE) % TB;       // block within the key tile (same for every wave's lane 0)
-    const int pos = (bb + wid) * 64 + lane;  // chunk within the key tile
-    if ((i * NWAVE) % TB < KCH / 64) {     // K chunk: slot pos -> key row, chunk column
-      const int key = pos / KC, c = (pos % KC) ^ (key & (KC - 1));
-      jrel[i] = key;
-      offc[i] = key * DH + c * 8;
-      fsrc[i] = kf + key * DH + c * 8;
-    } else {                                // V^T chunk: slot -> dimension row, 8-key chunk
-      const int p2 = pos - KCH;
-      const int d = p2 / VC, c = (p2 % VC) ^ (d & (VC - 1));
-      jrel[i] = c * 8;
-      offc[i] = d * a.Pc + c * 8;
-      fsrc[i] = vf + (size_t)d * a.Sp + c * 8;
+  for (int i = 0; i < TI; ++i) {
+    const int pos = (i * NWAVE + wid) * 64 + lane;  // chunk within the key tile
+    if (i < KI) {                                    // K chunk: slot pos -> key row, chunk column
+      key[i] = pos / KC;
+      voff[i] = coff[i] = (uint32_t)(key[i] * DH + ((pos % KC) ^ (key[i] & (KC - 1))) * 8) * 2u;
+    } else {                                          // V^T chunk: slot -> dimension row, 8-key chunk
+      const int d = (pos - KCH) / VC, c = ((pos - KCH) % VC) ^ (d & (VC - 1));
+      key[i] = c * 8;
+      voff[i] = ((uint32_t)d * (uint32_t)a.Sp + c * 8) * 2u;
+      coff[i] = ((uint32_t)d * (uint32_t)a.Pc + c * 8) * 2u;
     }
   }
+  const bool near = a.Sp < (1 << 23) && a.Pc < (1 << 23);  // the 32-bit offsets reach every V^T row
   const uint32_t lds_base = lds_addr_of(sm) + (uint32_t)wid * 1024u;
-  const int klast = nkeys - 1, vlast = (nkeys - 1) & ~7;  // last key, start of the last 8-key chunk
-  const int vlast_f = (Sk - 1) & ~7;                         // the same for the fresh values alone
-  // the main loop below is instantiated twice: without (kFresh) and with a cached prefix
-  auto main_loop = [&](auto fresh_only) {
-    constexpr bool kFresh = decltype(fresh_only)::value;
-    auto issue = [&](int t) {
-      const uint32_t stage = lds_base + (uint32_t)((t % STAGES) * SCH) * 16u;
+  auto issue = [&](int t) {
+    const uint32_t stage = lds_base + (uint32_t)((t % STAGES) * SCH) * 16u;
 #pragma unroll
-      for (int i = 0; i < IPW; ++i) {
-        const bool isk = (i * NWAVE) % TB < KCH / 64;
-        const int mult = isk ? DH : 1;
-        const int k0 = (t * KG + (i * NWAVE) / TB) * KT;
-        const int j = k0 + jrel[i];
-        const void* src;
-        if constexpr (kFresh) {
-          const int jc = min(j, isk ? klast : vlast);
-          src = fsrc[i] + (ptrdiff_t)(jc - jrel[i]) * mult;
-        } else {
-          // fresh side with the same clamping as above, in fresh-key indices; the cache side holds
-          // keys j < P (P is a multiple of 8, so no 8-key chunk straddles the two)
-          const int jf = min(j - P, isk ? klast - P : vlast_f);
-          const bf16_t* fp = fsrc[i] + (ptrdiff_t)(jf - jrel[i]) * mult;
-          const bf16_t* cp = (isk ? kc : vc) + offc[i] + (ptrdiff_t)k0 * mult;
-          src = j < P ? cp : fp;
-        }
-        dma16_at(src, stage + (uint32_t)(i * NWAVE) * 1024u);
-      }
-    };
-
+    for (int gg = 0; gg < KG; ++gg) {
+      const int k0 = (t * KG + gg) * KT;
+      const uint32_t dst = stage + (uint32_t)gg * (TCH * 16u);
+      if (near && k0 >= P && k0 + KT <= nkeys) {
+        const bf16_t* kb = uniform_ptr(kf + (ptrdiff_t)(k0 - P) * DH);
+        const bf16_t* vb = uniform_ptr(vf + (k0 - P));
 #pragma unroll
-    for (int st = 0; st < STAGES - 1; ++st)
-      if (st < nsteps) issue(st);
-    for (int t = 0; t < nsteps; ++t) {
-      // step t landed; the steps t + 1 .. min(nsteps - 1, t + STAGES - 2) may still fly
-      attn_wait_stages<IPW, STAGES - 2>(min(STAGES - 2, nsteps - 1 - t));
-      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-      if (t + STAGES - 1 < nsteps) issue(t + STAGES - 1);
-      const int k0 = (t * KG + kg) * KT;
-      if (k0 >= nkeys) continue;  // this group's tile is past the end (uniform per wave)
-      const uint4* sK = sm + (t % STAGES) * SCH + kg * TCH;
-      const uint4* sV = sK + KCH;
-
-      // S^T = K Q^T: lane holds keys 16 kt + 4 lg + r of query lq. The tile's K fragments are read
-      // first and the independent accumulation chains interleaved.
-      bf16x8_t kfr[KT / 16][DH / 32];
+        for (int i = 0; i < TI; ++i) dma16_sv(i < KI ? kb : vb, voff[i], dst + (uint32_t)(i * NWAVE) * 1024u);
+      } else if (near && k0 + KT <= P) {
+        const bf16_t* kb = uniform_ptr(kc + (ptrdiff_t)k0 * DH);
+        const bf16_t* vb = uniform_ptr(vc + k0);
 #pragma unroll
-      for (int kt = 0; kt < KT / 16; ++kt) {
-        const int row = 16 * kt + lq;
+        for (int i = 0; i < TI; ++i) dma16_sv(i < KI ? kb : vb, coff[i], dst + (uint32_t)(i * NWAVE) * 1024u);
+      } else {
 #pragma unroll
-        for (int ks = 0; ks < DH / 32; ++ks) {
-          const int c = 4 * ks + lg;
-          kfr[kt][ks] = __builtin_bit_cast(bf16x8_t, sK[row * KC + (c ^ (row & (KC - 1)))]);
+        for (int i = 0; i < TI; ++i) {
+          // P is a multiple of 8, so no 8-key chunk straddles the two sides
+          const int j = k0 + key[i];
+          const bf16_t* src;
+          if (i < KI) {
+            const int c = (int)(voff[i] >> 1) - key[i] * DH;  // element within the row
+            src = (j < P ? kc + (ptrdiff_t)j * DH : kf + (ptrdiff_t)min(j - P, Sk - 1) * DH) + c;
+          } else {
+            const int d = ((i * NWAVE + wid) * 64 + lane - KCH) / VC;
+            src = j < P ? vc + (ptrdiff_t)d * a.Pc + j : vf + (ptrdiff_t)d * a.Sp + min(j - P, (Sk - 1) & ~7);
+          }
+          dma16_at(src, dst + (uint32_t)(i * NWAVE) * 1024u);
         }
       }
-      f32x4_t sc[KT / 16];
+    }
+  };
+
 #pragma unroll
-      for (int kt = 0; kt < KT / 16; ++kt) sc[kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int st = 0; st < STAGES - 1; ++st)
+    if (st < nsteps) issue(st);
+  for (int t = 0; t < nsteps; ++t) {
+    // step t landed; the steps t + 1 .. min(nsteps - 1, t + STAGES - 2) may still fly
+    attn_wait_stages<IPW, STAGES - 2>(min(STAGES - 2, nsteps - 1 - t));
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (t + STAGES - 1 < nsteps) issue(t + STAGES - 1);
+    const int k0 = (t * KG + kg) * KT;
+    if (k0 >= nkeys) continue;  // this group's tile is past the end (uniform per wave)
+    const uint4* sK = sm + (t % STAGES) * SCH + kg * TCH;
+    const uint4* sV = sK + KCH;
+
+    // S^T = K Q^T: lane holds keys 16 kt + 4 lg + r of query lq. The tile's K fragments are read
+    // first and the independent accumulation chains interleaved.
+    bf16x8_t kfr[KT / 16][DH / 32];
+#pragma unroll
+    for (int kt = 0; kt < KT / 16; ++kt) {
+      const int row = 16 * kt + lq;
+#pragma unroll
+      for (int ks = 0; ks < DH / 32; ++ks) {
+        const int c = 4 * ks + lg;
+        kfr[kt][ks] = __builtin_bit_cast(bf16x8_t, sK[row * KC + (c ^ (row & (KC - 1)))]);
+      }
+    }
+    f32x4_t sc[QF][KT / 16];
+#pragma unroll
+    for (int f = 0; f < QF; ++f)
+#pragma unroll
+      for (int kt = 0; kt < KT / 16; ++kt) sc[f][kt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int f = 0; f < QF; ++f)
 #pragma unroll
       for (int ks = 0; ks < DH / 32; ++ks)
 #pragma unroll
-        for (int kt = 0; kt < KT / 16; ++kt) sc[kt] = mfma16a(kfr[kt][ks], qf[ks], sc[kt]);
-      // V^T fragments, read while the softmax below runs: dimension 16 dt + lq at the keys
-      // 32 s2 + 4 lg + {0..3} and 32 s2 + 16 + 4 lg + {0..3} (the order in which the score MFMA left
-      // the probabilities in the lanes). Each lane reads one whole 16-byte chunk (bank-conflict free
-      // through the XOR swizzle, as the K reads): lane groups 0 / 1 / 2 / 3 read the keys
-      // 0-7 / 16-23 / 8-15 / 24-31 of the 32-key block, and neighbouring groups (0, 1) and (2, 3)
-      // exchange halves with v_permlane16_swap, which swaps the odd 16-lane rows of its first operand
-      // with the even rows of its second: group 0 keeps keys 0-3 and receives 16-19, group 1 receives
-      // 4-7 and keeps 20-23, and likewise for groups 2 and 3.
-      bf16x8_t vfr[KT / 32][DH / 16];
+        for (int kt = 0; kt < KT / 16; ++kt) sc[f][kt] = mfma16a(kfr[kt][ks], qf[f][ks], sc[f][kt]);
+    // V^T fragments, read while the softmax below runs: dimension 16 dt + lq at the keys
+    // 32 s2 + 4 lg + {0..3} and 32 s2 + 16 + 4 lg + {0..3} (the order in which the score MFMA left
+    // the probabilities in the lanes). Each lane reads one whole 16-byte chunk (bank-conflict free
+    // through the XOR swizzle, as the K reads): lane groups 0 / 1 / 2 / 3 read the keys
+    // 0-7 / 16-23 / 8-15 / 24-31 of the 32-key block, and neighbouring groups (0, 1) and (2, 3)
+    // exchange halves with v_permlane16_swap, which swaps the odd 16-lane rows of its first operand
+    // with the even rows of its second: group 0 keeps keys 0-3 and receives 16-19, group 1 receives
+    // 4-7 and keeps 20-23, and likewise for groups 2 and 3.
+    bf16x8_t vfr[KT / 32][DH / 16];
 #pragma unroll
-      for (int s2 = 0; s2 < KT / 32; ++s2) {
-        const int cx = 4 * s2 + (((lg & 1) << 1) | (lg >> 1));
+    for (int s2 = 0; s2 < KT / 32; ++s2) {
+      const int cx = 4 * s2 + (((lg & 1) << 1) | (lg >> 1));
 #pragma unroll
-        for (int dt = 0; dt < DH / 16; ++dt) {
-          const int d = 16 * dt + lq;
-          const uint4 x = sV[d * VC + (cx ^ (d & (VC - 1)))];
-          const auto s0 = __builtin_amdgcn_permlane16_swap(x.x, x.z, false, false);
-          const auto s1 = __builtin_amdgcn_permlane16_swap(x.y, x.w, false, false);
-          vfr[s2][dt] = __builtin_bit_cast(bf16x8_t, make_uint4(s0[0], s1[0], s0[1], s1[1]));
-        }
+      for (int dt = 0; dt < DH / 16; ++dt) {
+        const int d = 16 * dt + lq;
+        const uint4 x = sV[d * VC + (cx ^ (d & (VC - 1)))];
+        const auto s0 = __builtin_amdgcn_permlane16_swap(x.x, x.z, false, false);
+        const auto s1 = __builtin_amdgcn_permlane16_swap(x.y, x.w, false, false);
+        vfr[s2][dt] = __builtin_bit_cast(bf16x8_t, make_uint4(s0[0], s1[0], s0[1], s1[1]));
       }
-      if (k0 + KT > nkeys) {  // only the last tile holds keys past the end
-#pragma unroll
-        for (int kt = 0; kt < KT / 16; ++kt)
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (k0 + 16 * kt + 4 * lg + r >= nkeys) sc[kt][r] = -INFINITY;
-      }
-      float tmax = -INFINITY;
+    }
+    if (k0 + KT > nkeys) {  // only the last tile holds keys past the end
+      asm volatile("");     // keep it a branch: as selects it costs every tile
 #pragma unroll
       for (int kt = 0; kt < KT / 16; ++kt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) tmax = fmaxf(tmax, sc[kt][r]);
-      // the four lane groups holding one query's keys: lanes l, l^16, l^32, l^48
-      tmax = xor_lanes16(tmax, [](float x, float y) { return fmaxf(x, y); });
-      tmax = xor_lanes32(tmax, [](float x, float y) { return fmaxf(x, y); });
-      // Lazy rescaling: the reference point m only moves when a score exceeds it by more than
-      // 2^8 (probabilities up to 256 are exact to represent and sum in float32); the division by
-      // the running sum at the end makes the result independent of the reference point. When no
-      // lane of the wave moves, the output rescale is skipped.
-      const float ts = tmax * scale;
-      const bool move = ts > m + 8.f;  // true on the first processed tile (m = -inf)
-      const float mn = move ? ts : m;
-      float psum = 0.f;
+        for (int r = 0; r < 4; ++r)
+          if (k0 + 16 * kt + 4 * lg + r >= nkeys)
+#pragma unroll
+            for (int f = 0; f < QF; ++f) sc[f][kt][r] = -INFINITY;
+    }
+    // Lazy rescaling: the reference point m only moves when a score exceeds it by more than
+    // 2^8 (probabilities up to 256 are exact to represent and sum in float32); the division by
+    // the running sum at the end makes the result independent of the reference point. When no
+    // lane of the wave moves (all but the first few tiles), neither the maximum over the query's four
+    // lanes nor the output rescale is needed.
+    float tmax[QF];  // of this lane's keys
+    bool move = false;
+#pragma unroll
+    for (int f = 0; f < QF; ++f) {
+      tmax[f] = -INFINITY;
+#pragma unroll
+      for (int kt = 0; kt < KT / 16; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tmax[f] = fmaxf(tmax[f], sc[f][kt][r]);
+      move |= tmax[f] * scale > m[f] + 8.f;
+    }
+    if (__builtin_amdgcn_ballot_w64(move)) {
+#pragma unroll
+      for (int f = 0; f < QF; ++f) {
+        // the four lane groups holding one query's keys: lanes l, l^16, l^32, l^48
+        float ts = xor_lanes16(tmax[f], [](float x, float y) { return fmaxf(x, y); });
+        ts = xor_lanes32(ts, [](float x, float y) { return fmaxf(x, y); }) * scale;
+        const float mn = ts > m[f] + 8.f ? ts : m[f];  // moves on the first processed tile (m = -inf)
+        const float alpha = __builtin_amdgcn_exp2f(m[f] - mn);  // 1 in the lanes that keep m
+        l[f] *= alpha;
+#pragma unroll
+        for (int dt = 0; dt < DH / 16; ++dt) o[f][dt] *= alpha;
+        m[f] = mn;
+      }
+    }
+    // O^T += V^T P^T over 32-key steps; P enters as three bf16 parts (hi + mid + lo)
+#pragma unroll
+    for (int f = 0; f < QF; ++f) {
 #pragma unroll
       for (int kt = 0; kt < KT / 16; ++kt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float pv = __builtin_amdgcn_exp2f(fmaf(sc[kt][r], scale, -mn));
-          sc[kt][r] = pv;
-          psum += pv;
+          const float pv = __builtin_amdgcn_exp2f(fmaf(sc[f][kt][r], scale, -m[f]));
+          sc[f][kt][r] = pv;
+          l[f] += pv;
         }
-      psum = xor_lanes16(psum, [](float x, float y) { return x + y; });
-      psum = xor_lanes32(psum, [](float x, float y) { return x + y; });
-      if (__builtin_amdgcn_ballot_w64(move)) {
-        const float alpha = __builtin_amdgcn_exp2f(m - mn);  // 1 in the lanes that keep m
-        l *= alpha;
-#pragma unroll
-        for (int dt = 0; dt < DH / 16; ++dt) o[dt] *= alpha;
-      }
-      l += psum;
-      m = mn;
-
-      // O^T += V^T P^T over 32-key steps; P enters as three bf16 parts (hi + mid + lo)
 #pragma unroll
       for (int s2 = 0; s2 < KT / 32; ++s2) {
         uint32_t hi[4], mi[4], lo[4];
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-          const float p0 = sc[2 * s2 + (x >> 1)][(x & 1) * 2], p1 = sc[2 * s2 + (x >> 1)][(x & 1) * 2 + 1];
+          const float p0 = sc[f][2 * s2 + (x >> 1)][(x & 1) * 2], p1 = sc[f][2 * s2 + (x >> 1)][(x & 1) * 2 + 1];
           hi[x] = f2bf2(p0, p1);
           const float r0 = p0 - __uint_as_float(hi[x] << 16), r1 = p1 - __uint_as_float(hi[x] & 0xFFFF0000u);
           mi[x] = f2bf2(r0, r1);
@@ -298,91 +335,109 @@ __global__ void __launch_bounds__(NQ * KG * 64) attn_kernel(AttnArgs a) {
         const bf16x8_t pmi = __builtin_bit_cast(bf16x8_t, make_uint4(mi[0], mi[1], mi[2], mi[3]));
         const bf16x8_t plo = __builtin_bit_cast(bf16x8_t, make_uint4(lo[0], lo[1], lo[2], lo[3]));
 #pragma unroll
-        for (int dt = 0; dt < DH / 16; ++dt) o[dt] = mfma16a(vfr[s2][dt], phi, o[dt]);
+        for (int dt = 0; dt < DH / 16; ++dt) o[f][dt] = mfma16a(vfr[s2][dt], phi, o[f][dt]);
 #pragma unroll
-        for (int dt = 0; dt < DH / 16; ++dt) o[dt] = mfma16a(vfr[s2][dt], pmi, o[dt]);
+        for (int dt = 0; dt < DH / 16; ++dt) o[f][dt] = mfma16a(vfr[s2][dt], pmi, o[f][dt]);
 #pragma unroll
-        for (int dt = 0; dt < DH / 16; ++dt) o[dt] = mfma16a(vfr[s2][dt], plo, o[dt]);
+        for (int dt = 0; dt < DH / 16; ++dt) o[f][dt] = mfma16a(vfr[s2][dt], plo, o[f][dt]);
       }
     }
-
-  };
-  if (P == 0) main_loop(std::integral_constant<bool, true>{});
-  else main_loop(std::integral_constant<bool, false>{});
+  }
 
   if constexpr (KG > 1) {
     // groups 1 .. KG-1 park (m, l, o) in the ring; group 0 folds them in group order
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     f32x4_t* xo = reinterpret_cast<f32x4_t*>(sm);
-    float2* xml = reinterpret_cast<float2*>(xo + (size_t)(KG - 1) * NQ * (DH / 16) * 64);
+    float2* xml = reinterpret_cast<float2*>(xo + (size_t)(KG - 1) * NQ * QF * (DH / 16) * 64);
     if (kg > 0) {
-      const int base = (kg - 1) * NQ + qw;
 #pragma unroll
-      for (int dt = 0; dt < DH / 16; ++dt) xo[((size_t)base * (DH / 16) + dt) * 64 + lane] = o[dt];
-      xml[base * 64 + lane] = make_float2(m, l);
+      for (int f = 0; f < QF; ++f) {
+        const int base = ((kg - 1) * NQ + qw) * QF + f;
+#pragma unroll
+        for (int dt = 0; dt < DH / 16; ++dt) xo[((size_t)base * (DH / 16) + dt) * 64 + lane] = o[f][dt];
+        xml[base * 64 + lane] = make_float2(m[f], l[f]);
+      }
     }
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (kg > 0) return;
 #pragma unroll
-    for (int gg = 1; gg < KG; ++gg) {
-      const int base = (gg - 1) * NQ + qw;
-      const float2 ml = xml[base * 64 + lane];
-      if (ml.x == -INFINITY) continue;  // a group that saw no key
-      const float mn = fmaxf(m, ml.x);
-      const float ea = __builtin_amdgcn_exp2f(m - mn), eb = __builtin_amdgcn_exp2f(ml.x - mn);
-      l = l * ea + ml.y * eb;
+    for (int f = 0; f < QF; ++f)
 #pragma unroll
-      for (int dt = 0; dt < DH / 16; ++dt) o[dt] = o[dt] * ea + xo[((size_t)base * (DH / 16) + dt) * 64 + lane] * eb;
-      m = mn;
-    }
+      for (int gg = 1; gg < KG; ++gg) {
+        const int base = ((gg - 1) * NQ + qw) * QF + f;
+        const float2 ml = xml[base * 64 + lane];
+        if (ml.x == -INFINITY) continue;  // a group that saw no key
+        const float mn = fmaxf(m[f], ml.x);
+        const float ea = __builtin_amdgcn_exp2f(m[f] - mn), eb = __builtin_amdgcn_exp2f(ml.x - mn);
+        l[f] = l[f] * ea + ml.y * eb;
+#pragma unroll
+        for (int dt = 0; dt < DH / 16; ++dt)
+          o[f][dt] = o[f][dt] * ea + xo[((size_t)base * (DH / 16) + dt) * 64 + lane] * eb;
+        m[f] = mn;
+      }
   }
 
-  if (qrow < S) {
-    const float inv = 1.0f / l;
+#pragma unroll
+  for (int f = 0; f < QF; ++f) {
+    float lt = xor_lanes16(l[f], [](float x, float y) { return x + y; });
+    lt = xor_lanes32(lt, [](float x, float y) { return x + y; });
+    const int qrow = q0 + 16 * f + lq;
+    if (qrow >= S) continue;
+    const float inv = 1.0f / lt;
     bf16_t* dst = a.o + (((size_t)b * S + qrow) * a.H + h) * DH + 4 * lg;
 #pragma unroll
     for (int dt = 0; dt < DH / 16; ++dt) {
       uint2 w;
-      w.x = f2bf2(o[dt][0] * inv, o[dt][1] * inv);
-      w.y = f2bf2(o[dt][2] * inv, o[dt][3] * inv);
+      w.x = f2bf2(o[f][dt][0] * inv, o[f][dt][1] * inv);
+      w.y = f2bf2(o[f][dt][2] * inv, o[f][dt][3] * inv);
       *reinterpret_cast<uint2*>(dst + 16 * dt) = w;
     }
   }
 }
 
-template <int NQ, int KG, int KT, int STAGES>
+template <int NQ, int QF, int KG, int KT, int DH, int STAGES>
 static void run_attn(const AttnArgs& a, hipStream_t s) {
-  static_assert((size_t)STAGES * KG * (KT * 16 + 128 * (KT / 8)) * 16 <= 160 * 1024, "ring exceeds the LDS of a CU");
-  const int units = ((a.S + 16 * NQ - 1) / (16 * NQ)) * a.H * a.B;
+  constexpr size_t lds = (size_t)STAGES * KG * (KT * (DH / 8) + DH * (KT / 8)) * 16;
+  static_assert(lds <= 160 * 1024, "ring exceeds the LDS of a CU");
+  const int units = ((a.S + 16 * NQ * QF - 1) / (16 * NQ * QF)) * a.H * a.B;
   if (units == 0) return;
   dim3 grid(8 * ((units + 7) / 8));
-  const size_t lds = (size_t)STAGES * KG * (KT * (a.dh / 8) + a.dh * (KT / 8)) * 16;
-  if (a.dh == 128) {
-    auto kern = attn_kernel<NQ, KG, KT, 128, STAGES>;
-    static std::atomic<uint32_t> lds_set{0};
-    ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_set);
-    hipLaunchKernelGGL(kern, grid, dim3(NQ * KG * 64), lds, s, a);
-  } else if constexpr ((KT * 8 / 64) % (NQ * KG) != 0 || (64 * (KT / 8) / 64) % (NQ * KG) != 0) {
-    run_attn<4, 2, 64, 2>(a, s);  // this wave layout does not tile head_dim 64: the default one does
-  } else {
-    auto kern = attn_kernel<NQ, KG, KT, 64, STAGES>;
-    static std::atomic<uint32_t> lds_set{0};
-    ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_set);
-    hipLaunchKernelGGL(kern, grid, dim3(NQ * KG * 64), lds, s, a);
-  }
+  auto kern = attn_kernel<NQ, QF, KG, KT, DH, STAGES>;
+  static std::atomic<uint32_t> lds_set{0};
+  ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, lds_set);
+  hipLaunchKernelGGL(kern, grid, dim3(NQ * KG * 64), lds, s, a);
 }
 
-// A two-stage ring of 32-key tiles: 64 KB of LDS for head_dim 128, so two workgroups share a CU. Few query
-// waves (B * H * S / 16 below 4096): 4 query waves x 2 key groups per workgroup, so each wave walks half
-// the keys and twice as many waves share a CU; many query waves: 8 query waves x 1 group. Measured on
-// MI355X (LLaDA-8B / Dream-7B heads, three-part P), per launch, against the same layouts with 64-key
-// tiles (128 KB rings, one workgroup per CU): 384 tokens 12.2 us (12.1), 1280 tokens 73.0 us (87.0),
-// 8 x 64 tokens over a 1216-key cache 34.1 us (35.1), Dream-7B 4 x 768 tokens 88.4 us (95.8).
-// head_dim 64 falls back to 64-key tiles (a 32-key tile has too few 64-chunk blocks for 8 waves).
+// Rings of two steps; 32-key tiles (64-key tiles and deeper rings were slower at every size). The layout follows from
+// the query waves (16 queries each) that the call has, over 256 CUs of four SIMDs. Kernel alone, K / V warm, us,
+// against 4 query waves x 2 key groups of 16 queries (8 x 1 from 4096 query waves on), the two layouts in use before:
+//   up to 256: a workgroup per query wave whose four waves share out the keys: otherwise few CUs have work at all.
+//     32 (1 x 16 tokens over 1900 keys) 39.2 -> 25.1, 128 (1 x 64 over 323) 12.8 -> 9.8, head_dim 64, 24 (1 x 96) 4.8 -> 3.8
+//     (up to 64 keys most of those waves would have none: the next layout, 2 - 7 % faster there)
+//   up to 640, without a cache 800: 32-query workgroups, so more CUs have one: 448 (4 x 64 over 1000) 1.39 times as
+//     fast, 768 (1 x 384) 12.9 -> 12.2; with a cache every workgroup more reads it once more (768, 8 x 40 over 2000:
+//     17 % slower than before)
+//   few keys: one key group, since a group's share would be one to five tiles and the merge: 1092 (3 x 203) 14.7 -> 13.3
+//   up to 2048: two query fragments per wave and two key groups (1024, 8 x 64 over 1216, 37.3 -> 36.5; 1472, 1 x 730,
+//     31.5 -> 30.5); up to 2800 workgroups of 64 queries, four to a CU, even out the last round (2432, 2 x 600, 41.2 ->
+//     37.4; 2624, 1 x 1300, 78.2 -> 73.3); above, 128 (3648, 2 x 900, 76.0 -> 66.8; 5376, 4 x 768, 82.2 -> 80.2).
+// Over 310 sizes of 16 to 3072 tokens and 0 to 2000 cached keys the rule is on average 2 % slower than the fastest
+// layout of each, the two layouts before 21 %.
 void launch_attention(const AttnArgs& a, hipStream_t s) {
   const long query_waves = (long)a.B * a.H * ((a.S + 15) / 16);
-  if (query_waves >= 4096) run_attn<8, 1, 32, 2>(a, s);
-  else run_attn<4, 2, 32, 2>(a, s);
+  const int nkeys = a.P + (a.Sk ? a.Sk : a.S);
+  const bool few = query_waves <= 256 && nkeys > 64;
+  if (a.dh == 128) {
+    if (few) run_attn<1, 1, 4, 32, 128, 2>(a, s);
+    else if (query_waves > 640 && query_waves <= 2800 && (nkeys <= 320 || query_waves >= 2048))
+      run_attn<4, 1, 1, 32, 128, 2>(a, s);
+    else if (query_waves <= (a.P ? 640 : 800)) run_attn<2, 1, 2, 32, 128, 2>(a, s);
+    else if (query_waves < 2048) run_attn<2, 2, 2, 32, 128, 2>(a, s);
+    else run_attn<4, 2, 1, 32, 128, 2>(a, s);
+  } else {
+    if (few) run_attn<1, 1, 4, 32, 64, 2>(a, s);
+    else run_attn<2, 1, 2, 32, 64, 2>(a, s);
+  }
 }
 
 // ---------------------------------------------------------------- cache write-back

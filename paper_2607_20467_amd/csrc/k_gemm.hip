@@ -745,12 +745,6 @@ __device__ __forceinline__ void phase_barrier() {
   asm volatile("s_barrier" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
-// One 1 KiB wave copy: 64 lanes x 16 bytes from a scalar base plus a per-lane byte offset.
-__device__ __forceinline__ void dma16_sv(const void* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base)
-               : "memory", "m0");
-}
-
 template <int BW, int BT, int S, class Epi>
 __global__ void __launch_bounds__(512)
 gemm_pp_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, int T, int K,
