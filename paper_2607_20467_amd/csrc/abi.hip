@@ -282,14 +282,16 @@ int run_layer(const Model* m, int l, int B, int S, const dcl_kv* kv, void* ws, c
   qo.Sk = L.Sk;
   qo.koff = L.koff;
   qo.pos0 = P;
+  const int Pc = kv ? (kv->capacity ? kv->capacity : P) : 0;
+  if (kv && L.koff > 0) {  // the newest P mod 8 cached keys/values in front of the fresh ones
+    qo.kc = static_cast<const bf16_t*>(kv->k[l]);
+    qo.vc = static_cast<const bf16_t*>(kv->v[l]);
+    qo.Pc = Pc;
+  }
   {
     PROF(P_QKV);
     gemm_qkv(at<bf16_t>(wb, lo.wqkv), u, m->qkv_rows(), T, d, qo, s);
   }
-  const int Pc = kv ? (kv->capacity ? kv->capacity : P) : 0;
-  if (kv && L.koff > 0)  // the newest P mod 8 cached keys/values in front of the fresh ones
-    launch_kv_carry(static_cast<const bf16_t*>(kv->k[l]), static_cast<const bf16_t*>(kv->v[l]), qo.k, qo.vt, B,
-                    c.n_kv_heads, L.Sk, L.Sp, dh, P, Pc, s);
   if (taps) {
     tap(taps->q, qo.q, (size_t)T * c.n_heads * dh * 2, s);
     tap(taps->k, qo.k, (size_t)B * L.Sk * c.n_kv_heads * dh * 2, s);

@@ -122,6 +122,10 @@ struct QkvOut {
   const float2* rope;    // [max_pos, dh/2] (cos, sin) or null (RoPE off)
   int H, Hkv, dh, S, Sp, pos0;
   int Sk = 0, koff = 0;  // fresh key rows per (b, kv head) and the slot of token 0 (0, 0: Sk = S)
+  // with koff > 0: the cache [B,Hkv,Pc,dh] / [B,Hkv,dh,Pc], whose keys [pos0 - koff, pos0) are copied into slots
+  // [0, koff) of the fresh buffers
+  const bf16_t *kc = nullptr, *vc = nullptr;
+  int Pc = 0;
 };
 struct LmOut {
   float *pm1, *pm2, *ps;
@@ -160,10 +164,6 @@ struct AttnArgs {
                                  // ragged prefix are carried into the front of k / vt (Sk = P mod 8 + S)
 };
 void launch_attention(const AttnArgs& a, hipStream_t s);
-// The koff = P mod 8 newest cached keys [P - koff, P) and their values into slots [0, koff) of the fresh
-// buffers k [B,Hkv,Sk,dh] and vt [B,Hkv,dh,Sp] (cache kc [B,Hkv,Pc,dh], vc [B,Hkv,dh,Pc]).
-void launch_kv_carry(const bf16_t* kc, const bf16_t* vc, bf16_t* k, bf16_t* vt, int B, int Hkv, int Sk, int Sp,
-                     int dh, int P, int Pc, hipStream_t s);
 // Fresh keys k [B,Hkv,Sk,dh] and values vt [B,Hkv,dh,Sp] of tokens 0..S-1 (slots koff + s) into a cache at
 // positions [P, P + S) (kc [B,Hkv,Pc,dh], vc [B,Hkv,dh,Pc]).
 void launch_kv_writeback(const bf16_t* k, const bf16_t* vt, bf16_t* kc, bf16_t* vc, int B, int Hkv, int S, int Sk,

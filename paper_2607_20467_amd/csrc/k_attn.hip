@@ -471,37 +471,4 @@ void launch_kv_writeback(const bf16_t* k, const bf16_t* vt, bf16_t* kc, bf16_t* 
                      Pc);
 }
 
-// ---------------------------------------------------------------- carried cache keys
-// A cached prefix whose length P is not a multiple of 8 ends inside an 8-key chunk. Attention reads the
-// cache only in whole chunks, so the koff = P mod 8 newest cached keys (and values) are copied in front
-// of the fresh ones: slots [0, koff) of k [BH, Sk, dh] and of every v^T row (pitch Sp). One thread per
-// element.
-__global__ void __launch_bounds__(256) kv_carry_kernel(const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
-                                                      bf16_t* __restrict__ k, bf16_t* __restrict__ vt, int BH, int Sk,
-                                                      int Sp, int dh, int P, int Pc, int koff) {
-  const size_t n = (size_t)BH * koff * dh;  // as many key elements as value elements
-  const size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (i >= 2 * n) return;
-  const int P8 = P - koff;
-  if (i < n) {
-    const size_t d = i % dh, rest = i / dh;
-    const size_t j = rest % koff, bh = rest / koff;
-    k[(bh * Sk + j) * dh + d] = kc[(bh * Pc + P8 + j) * dh + d];
-  } else {
-    const size_t e = i - n;
-    const size_t j = e % koff, rest = e / koff;  // rest = bh * dh + d
-    vt[rest * Sp + j] = vc[rest * Pc + P8 + j];
-  }
-}
-
-void launch_kv_carry(const bf16_t* kc, const bf16_t* vc, bf16_t* k, bf16_t* vt, int B, int Hkv, int Sk, int Sp,
-                     int dh, int P, int Pc, hipStream_t s) {
-  const int koff = P % 8;
-  if (koff == 0) return;
-  const size_t n = 2 * (size_t)B * Hkv * koff * dh;
-  hipLaunchKernelGGL(kv_carry_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, kc, vc, k, vt, B * Hkv, Sk,
-                     Sp, dh, P, Pc, koff);
-}
-
-
 }  // namespace dcl
