@@ -52,10 +52,15 @@ __device__ __forceinline__ void dma16_at(const void* g, uint32_t lds_addr) {
 __device__ __forceinline__ uint32_t lds_addr_of(const void* lds) {
   return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)lds);
 }
-// One 1 KiB wave copy: 64 lanes x 16 bytes from a scalar base plus a per-lane byte offset.
+// One 1 KiB wave copy: 64 lanes x 16 bytes from a scalar base plus a per-lane byte offset. A VALU instruction that
+// wrote the base (readfirstlane, the restore of a spilled register) must be 5 wait states away from a vector-memory
+// instruction that reads it, and neither the hardware nor, inside assembly, the compiler sees to that. Scalar
+// instructions are interlocked on both sides, so the load takes the base through one; it is also the wait state
+// between the write of m0 and the load. (s_nop 3 in its place: 8 x 64 tokens over 1216 keys 0.7 % slower.)
 __device__ __forceinline__ void dma16_sv(const void* base, uint32_t voff, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(voff), "s"(base)
-               : "memory", "m0");
+  const void* b;
+  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+               : "=&s"(b) : "s"(lds_addr), "v"(voff), "s"(base) : "memory", "m0");
 }
 __device__ __forceinline__ void dma16(const void* g, const void* lds) { dma16_at(g, lds_addr_of(lds)); }
 
