@@ -63,16 +63,20 @@ struct EpiResid {
   }
 };
 
-// g / (1 + e^-g): the quotient by reciprocal and one correction step (exact remainder), within an ulp of the
-// IEEE division it replaces at two thirds of its instructions. Past 2^126 (g < -87.3) the remainder would leave
-// the normal range (or be inf * 0), and the plain product is kept.
-__device__ __forceinline__ float silu(float g) {
+// g / (1 + e^-g): the quotient by reciprocal and one correction step (exact remainder), at two thirds of the IEEE
+// division's instructions. It is within an ulp of that where the denominator is below 2^126 (g > -87.3; past it the
+// reciprocal and the remainder leave the normal range) and g is finite (the correction of inf is NaN). `range` adds up
+// the denominators, and a correction that is not finite makes it NaN: with range < 2^126 every quotient it has seen holds.
+constexpr float kSiluRange = 0x1p126f;
+__device__ __forceinline__ float silu(float g, float& range) {
   const float x = 1.0f + __expf(-g);
   const float r = __builtin_amdgcn_rcpf(x);
   const float q = g * r;
   const float c = fmaf(fmaf(-q, x, g), r, q);
-  return x < 0x1p126f ? c : q;
+  range = fmaf(c, 0.0f, range + x);
+  return c;
 }
+__device__ __forceinline__ float silu_ieee(float g) { return g / (1.0f + __expf(-g)); }
 
 // Transposes over the four 16-lane groups. Lane group p holds piece p (rows 4 p ..) of each fragment of a wave's
 // column; a store needs consecutive rows of one fragment in one lane.
@@ -105,25 +109,35 @@ struct EpiSwiglu {
       const int t = tl + 16 * JS * j;
       if (tb + 16 * JS * j >= T) continue;  // wave-uniform: every lane takes part in the swaps
       bf16_t* dst = a + (size_t)t * F;
-      auto pair = [&](int i) {
+      uint32_t h[SW];  // this lane's piece of each fragment: two products
+      float range = 0.f;
+#pragma unroll
+      for (int i = 0; i < SW; ++i) {
         const f32x4_t v = acc[i][j];
-        return f2bf2(silu(v[0]) * v[1], silu(v[2]) * v[3]);
-      };
+        h[i] = f2bf2(silu(v[0], range) * v[1], silu(v[2], range) * v[3]);
+      }
+      if (!(range < kSiluRange)) {
+#pragma unroll
+        for (int i = 0; i < SW; ++i) {
+          const f32x4_t v = acc[i][j];
+          h[i] = f2bf2(silu_ieee(v[0]) * v[1], silu_ieee(v[2]) * v[3]);
+        }
+      }
 #pragma unroll
       for (int i = 0; i + 4 <= SW; i += 4) {
-        const uint4 x = gather_pieces(pair(i), pair(i + 1), pair(i + 2), pair(i + 3));
+        const uint4 x = gather_pieces(h[i], h[i + 1], h[i + 2], h[i + 3]);
         const int w = wb + 16 * (i + p);
         if (t < T && w < Nw) *reinterpret_cast<uint4*>(dst + (w >> 1)) = x;
       }
       if constexpr (SW % 4 >= 2) {
         constexpr int i = SW / 4 * 4;
-        const uint2 x = gather_pieces(pair(i), pair(i + 1));
+        const uint2 x = gather_pieces(h[i], h[i + 1]);
         const int w = wb + 16 * (i + (p & 1));
         if (t < T && w < Nw) *reinterpret_cast<uint2*>(dst + (w >> 1) + 4 * (p >> 1)) = x;
       }
       if constexpr (SW % 2) {
         const int w = wb + 16 * (SW - 1) + 4 * p;
-        if (t < T && w < Nw) *reinterpret_cast<uint32_t*>(dst + (w >> 1)) = pair(SW - 1);
+        if (t < T && w < Nw) *reinterpret_cast<uint32_t*>(dst + (w >> 1)) = h[SW - 1];
       }
     }
   }

@@ -107,6 +107,46 @@ def test_layer_tiles(d, F, H, T):
     _check("r_out", b["r_out"].view(T, d), r_mid + y, e + (F + 6) * 2.0 ** -23 * r_mid.abs(), False)
 
 
+# gates around the ends of silu's range in float32 (its denominator passes 2^126 at -87.3 and the largest float at
+# -88.7), beside infinities and ordinary ones; 89 ids a round, so every row of a fragment meets every gate
+GATES = [float("inf"), -88.5, 88.5, -88.0, 3e38, -87.5, 0.0, -87.0, 1e-30, -86.5, -1.0, -89.0, 2.0, -200.0, -0.0, -3e38,
+         1e38] + [(i - 36) / 4.0 for i in range(72)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("T", [5, 64, 129, 200, 513])
+def test_swiglu_gates_at_the_ends_of_the_range(T):
+    """g / (1 + e^-g) of given gates: +inf stays +inf and leaves its neighbours alone, and the quotients past 2^126 keep
+    their bits (relative error of the float32 exponential and quotient as in test_layer_tiles)."""
+    import torch
+    import paper_2607_20467_amd as dcl
+    d, F = 384, 6144
+    g = _geom(d, F, 1)
+    w = _weights(g, torch.Generator(device="cuda").manual_seed(T))
+    w[7].zero_()                                            # W_o: the residual stream reaches the MLP unchanged
+    gates = torch.tensor([GATES[i % len(GATES)] for i in range(F)], dtype=torch.float64).to(torch.bfloat16).cuda()
+    up = torch.tensor([[1.0, -0.5, 3.0][i % 3] for i in range(F)], dtype=torch.float64).to(torch.bfloat16).cuda()
+    w[8].zero_()
+    w[9].zero_()
+    w[8][:, 0], w[9][:, 0] = gates, up
+    run = dcl.Runner(g, w, max_positions=2048, rope_enabled=False)
+    taps = {k: torch.full((T * n,), -1, dtype=torch.int16, device="cuda") for k, n in (("u2", d), ("a", F))}
+    ws, n = run.workspace(1, T)
+    dcl.dcl_debug_layer(run.model, 1, T, None, 0, torch.ones((T, d), device="cuda"), taps, ws, n)
+    assert bool((taps["u2"].view(torch.bfloat16) == 1).all())
+    a = taps["a"].view(torch.bfloat16).view(T, F).double()
+    gt = gates.double()
+    den = 1 + torch.exp(-gt)
+    den[den > torch.finfo(torch.float32).max] = float("inf")   # the float32 denominator
+    want = gt / den * up.double()
+    inf = gt.isinf()
+    assert bool((a[:, inf] == want[inf]).all()), "silu(+inf) up"
+    big = want.abs() > torch.finfo(torch.bfloat16).max
+    bad = ~((a - want).abs() <= want.abs() * ((gt.abs() + 8) * 2.0 ** -21 + 2.0 ** -8))      # NaN counts as bad
+    bad[:, inf | big] = False
+    assert not bool(bad.any()), f"gates {gt[bad.any(0)].unique().tolist()} outside the bound"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("V,d,n", HEADS)
 def test_head_tiles(V, d, n):
