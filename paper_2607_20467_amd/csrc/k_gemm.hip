@@ -605,8 +605,14 @@ __device__ __forceinline__ void wait_stages(int n) {  // all but this wave's new
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Waves per SIMD that the registers must allow. The K-tail kernel's 64 KB ring lets a CU hold two workgroups of two waves
+// per SIMD, which takes at most 128 registers; one more halves the waves (q/k/v of 1280 tokens x 6144 x 2000: 75 us with
+// 129 registers, 51 with 128). Its LM head needs 145.
+template <class Epi, bool KTAIL>
+constexpr int kMinWaves = KTAIL && Epi::kKind != kEpiLm ? 4 : 1;
+
 template <int BW, int BT, int KD, int STAGES, int WW, int WT, class Epi, bool KTAIL>
-__global__ void __launch_bounds__(WW * WT * 64)
+__global__ void __launch_bounds__(WW * WT * 64, (kMinWaves<Epi, KTAIL>))
 gemm_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, int T, int K,
             const int32_t* __restrict__ t_count, int nsplit, Epi epi) {
   constexpr int NWAVE = WW * WT;

@@ -1,4 +1,5 @@
-"""Wait states that the hardware does not enforce, checked on the library's own gfx950 code.
+"""Wait states that the hardware does not enforce, and registers that occupancy rests on, checked on the library's own
+gfx950 code.
 
 A VALU write of a scalar register needs 5 wait states before a vector-memory instruction reads that register. The
 compiler inserts them between instructions it knows; it does not look into inline assembly, so the copies written
@@ -79,14 +80,14 @@ def hazards(listing):
     return found
 
 
-def _listing(tmp_path, lib):
+def _listing(tmp_path, lib, tool=OBJDUMP, option="-d"):
     if not os.path.exists(OBJDUMP):
         pytest.skip("llvm-objdump is not installed")
     copy = shutil.copy(lib, tmp_path / "lib.so")              # the code objects are extracted beside it
     subprocess.run([OBJDUMP, "--offloading", copy], check=True, capture_output=True)
     objs = sorted(p for p in os.listdir(tmp_path) if p.endswith("gfx950"))
     assert objs, "no gfx950 code object in the library"
-    return [subprocess.run([OBJDUMP, "-d", str(tmp_path / o)], check=True, capture_output=True, text=True).stdout
+    return [subprocess.run([tool, option, str(tmp_path / o)], check=True, capture_output=True, text=True).stdout
             for o in objs]
 
 
@@ -110,3 +111,15 @@ def test_vector_memory_waits_for_scalar_registers_written_by_valu(tmp_path):
         bad += hazards(text)
     assert loads > 1000, "the library's direct-to-LDS copies were not found"
     assert not bad, f"{len(bad)} reads with fewer than {WAIT} wait states, first: {bad[:3]}"
+
+
+def test_tail_gemms_leave_room_for_two_workgroups(tmp_path):
+    """Two workgroups of eight waves on a CU take at most 128 vector registers per wave. The LM head's tail kernel needs
+    more and runs one."""
+    import paper_2607_20467_amd as dcl
+    regs = {}
+    for text in _listing(tmp_path, dcl.library_path(), os.path.join(os.path.dirname(OBJDUMP), "llvm-readobj"), "--notes"):
+        for name, n in re.findall(r"\.name: +(_Z\S+)(?:(?!\.name:).)*?\.vgpr_count: +(\d+)", text, re.S):
+            regs[name] = int(n)
+    tail = {k: v for k, v in regs.items() if re.search(r"gemm_kernel.*Lb1E", k) and "EpiLm" not in k}
+    assert len(tail) >= 5 and max(tail.values()) <= 128, tail
