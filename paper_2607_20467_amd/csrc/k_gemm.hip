@@ -38,11 +38,11 @@ __device__ __forceinline__ f32x4_t mfma16(const bf16x8_t& a, const bf16x8_t& b, 
 // apply(): acc[i][j] holds C[wb + 16 i + 4 (lane/16) + r][tb + 16 JS j + lane%16], r = 0..3 (JS: the stride
 // of a wave's token fragments, in fragments).
 
-enum { kEpiPlain, kEpiLm, kEpiDebug };
+enum { kEpiPlain, kEpiResid, kEpiLm, kEpiDebug };
 
 struct EpiResid {
   float* r;
-  static constexpr int kKind = kEpiPlain;
+  static constexpr int kKind = kEpiResid;
   template <int SW, int ST, int JS = 1>
   __device__ __forceinline__ void apply(f32x4_t (&acc)[SW][ST], int wb, int tb, int lane, int Nw, int T, int, int) const {
     const int wq = wb + 4 * (lane >> 4), tl = tb + (lane & 15);
@@ -310,7 +310,7 @@ struct EpiF32 {
 struct EpiPartial {
   float* P;
   size_t stride;
-  static constexpr int kKind = kEpiPlain;
+  static constexpr int kKind = kEpiResid;
   template <int SW, int ST, int JS = 1>
   __device__ __forceinline__ void apply(f32x4_t (&acc)[SW][ST], int wb, int tb, int lane, int Nw, int T, int,
                                         int split) const {
@@ -986,6 +986,7 @@ static const TileCfg kCfgs[] = {
     {128, 192, 64, 4, 2, 4, 1}, {128, 128, 64, 4, 2, 4, 1}, {128, 64, 64, 3, 2, 4, 1},
     // one token tile of weights streamed (stream_cfg)
     {32, 32, 128, 4, 2, 2, 0},  {32, 64, 128, 6, 1, 4, 0},  {48, 64, 128, 5, 1, 4, 0},  {96, 64, 128, 3, 2, 2, 0},
+    {128, 192, 64, 3, 2, 4, 0},  // residual GEMMs with full token tiles (plan_gemm)
 };
 constexpr int kModelCfgs = 15;  // the first ones: those that the cost model chooses from
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
@@ -1014,7 +1015,8 @@ static const TileCost kCost[2 * kModelCfgs] = {
 // Estimated time (us) of a GEMM with configuration `ci` and n K splits: launch + rounds of resident workgroups,
 // each round a unit's fixed part plus its stages. A stage also takes no less than the weight rows that the
 // resident workgroups share out need from HBM (each distinct row once) at 5.4 TB/s, the rate the streaming
-// cases reach. Split-K slices are charged the read of the next RMSNorm (5 TB/s).
+// cases reach. Split-K slices are charged the read of the next RMSNorm (5 TB/s: 25 MB of them
+// lengthen a norm of 384 tokens by 4.5 us, 63 MB one of 1280 by 12.5).
 static double plan_cost(int ci, bool lm, int n, int Nw, int T, int K) {
   const TileCfg& c = kCfgs[ci];
   const TileCost& k = kCost[(lm ? kModelCfgs : 0) + ci];
@@ -1074,6 +1076,11 @@ GemmPlan plan_gemm(int Nw, int T, int K, int force_bw, int max_split) {
       }
     }
   }
+  // 128 x 192 tiles of a residual GEMM whose last token tile has no empty fragment: the two-phase kernel has nothing
+  // to skip there, and the ring kernel's three stages are 1 - 4 % faster than its four (in the layer: 4096 x 384 x 4096
+  // 23.7 -> 22.7 us, K = 12288 47.9 -> 47.3, 3584 x 384 x 18944 64.6 -> 63.3; with a partly filled last tile up to 13 %
+  // slower, 3584 x 448 x 18944).
+  if (best.cfg == 12 && max_split > 1 && (T - 1) % 192 >= 128) best.cfg = 19;
   const TileCfg& c = kCfgs[best.cfg];
   best.tiles = ((Nw + c.bw - 1) / c.bw) * ((T + c.bt - 1) / c.bt);
   return best;
@@ -1168,15 +1175,15 @@ static bool run_pp(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const
   return true;
 }
 
-static_assert(kNumCfgs == 19, "run_plan dispatches every configuration of kCfgs");
+static_assert(kNumCfgs == 20, "run_plan dispatches every configuration of kCfgs");
 
 // Whether the epilogue has a kernel for configuration CI: the LM head runs only the layouts of lm_ok, the debug
-// logits (test support) one tile, and 128 x 64 tiles serve only the LM head.
+// logits (test support) one tile, 128 x 64 tiles serve only the LM head and the 128 x 192 ring only residual GEMMs.
 template <class Epi, int CI>
 constexpr bool has_cfg() {
   if (Epi::kKind == kEpiLm) return (CI >= 3 && CI <= 6) || CI == 11 || CI == 13 || CI == 14;
   if (Epi::kKind == kEpiDebug) return CI == 13;
-  return CI != 14;
+  return CI != 14 && (CI != 19 || Epi::kKind == kEpiResid);
 }
 
 template <class Epi>
@@ -1208,6 +1215,7 @@ static void run_plan(const GemmPlan& p, const bf16_t* W, const bf16_t* X, int Nw
       DCL_RING(16, 32, 64, 128, 6, 1, 4);
       DCL_RING(17, 48, 64, 128, 5, 1, 4);
       DCL_RING(18, 96, 64, 128, 3, 2, 2);
+      DCL_RING(19, 128, 192, 64, 3, 2, 4);
     }
   }
 #undef DCL_RING

@@ -16,6 +16,7 @@ from helpers import CONF_TOL, LOGIT_TOL, TIE_GAP
 # (d_model, d_ffn, heads x 64, tokens): the plans of their four GEMMs cover every configuration (checked below)
 LAYERS = [(384, 6144, 4, 17), (384, 6144, 4, 129), (384, 6144, 4, 200), (384, 6144, 4, 385), (384, 6144, 4, 449),
           (384, 6144, 4, 513), (384, 6144, 4, 700), (384, 6144, 4, 770), (384, 6144, 4, 1025), (384, 6144, 16, 1300),
+          (1152, 3072, 2, 775), (1024, 3072, 2, 1361), (2048, 3072, 4, 705), (2048, 3072, 4, 768),
           (256, 3072, 4, 700), (1024, 3072, 16, 1025), (1024, 3072, 16, 600), (2048, 3072, 16, 1025),
           (1152, 12288, 2, 497), (400, 208, 4, 131),
           # one token tile (32 x 32 tiles; 32, 48 and 96 rows x 64 tokens): remainders of rows and tokens, short K
@@ -38,7 +39,7 @@ def _plans(dcl):
 def test_shapes_cover_every_configuration():
     import paper_2607_20467_amd as dcl
     layer, head = _plans(dcl)
-    want = set(range(19)) - {6, 14}
+    want = set(range(20)) - {6, 14}
     assert layer >= want, f"configurations {sorted(want - layer)} not covered"
     assert head >= {0, 3, 4, 5, 6, 14}, f"head configurations covered: {sorted(head)}"
 
