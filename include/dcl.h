@@ -290,8 +290,10 @@ dcl_status dcl_debug_layer(dcl_model_t model, int32_t B, int32_t S, const dcl_kv
                            const float* r_in, dcl_layer_taps taps, void* ws, size_t ws_bytes, hipStream_t stream);
 
 /* Test support (host only): the tile plan a GEMM of Nw weight rows, T tokens and depth K runs with.
- * lm_head = 1 asks for the fused LM-head plan (vocabulary tiles of 128 ids), otherwise the plan of a
- * residual GEMM allowed max_split (1..4) K-split slices. info (host int32[8]) receives
+ * lm_head = 1 asks for the fused LM head on T given rows (dcl_score_hidden; vocabulary tiles of 128 ids),
+ * 2 for that of a step over T tokens that are all scored (with fewer scored rows the step runs the same
+ * configuration; under that of 256 x 256 tiles the scored rows choose 192 or 256 tokens per tile), 0 for the
+ * plan of a GEMM allowed max_split K-split slices (1: q/k/v and gate/up, 4: residual). info (host int32[8]) receives
  * {configuration index, K-split slices, weight rows, tokens, K depth per stage, stages, waves along
  * the weight rows, waves along the tokens}; an LM-head plan whose weight rows per wave equal 128 has
  * every wave own a whole vocabulary tile. */

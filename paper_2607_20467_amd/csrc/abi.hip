@@ -885,9 +885,12 @@ dcl_status dcl_debug_gemm_plan(int32_t Nw, int32_t T, int32_t K, int32_t lm_head
   if (!info) return fail(DCL_E_ARG, "info is NULL");
   if (Nw < 1 || T < 1 || K < 1 || max_split < 1 || max_split > kMaxSplit)
     return fail(DCL_E_ARG, "Nw=%d T=%d K=%d max_split=%d outside their ranges", Nw, T, K, max_split);
-  const GemmPlan p = plan_gemm(Nw, T, K, lm_head ? kLmTile : 0, lm_head ? 1 : max_split);
+  int tokens = 0;
+  const GemmPlan p = lm_head == 2 ? plan_lmhead_step(Nw, T, K, &tokens)
+                                  : plan_gemm(Nw, T, K, lm_head ? kLmTile : 0, lm_head ? 1 : max_split);
   int shape[6];
   gemm_cfg_shape(p.cfg, shape);
+  if (tokens) shape[1] = tokens;
   info[0] = p.cfg;
   info[1] = p.nsplit;
   for (int i = 0; i < 6; ++i) info[2 + i] = shape[i];

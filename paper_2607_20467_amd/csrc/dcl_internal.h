@@ -146,8 +146,10 @@ struct GemmPlan {
 };
 // force_bw: restrict to tiles of that many weight rows (0: any); max_split: largest K-split factor.
 GemmPlan plan_gemm(int Nw, int T, int K, int force_bw, int max_split);
-// The LM head's plan where only the device knows how many of the T rows are scored.
-GemmPlan plan_lmhead_counted(int V, int T, int K);
+// A step's LM head over T tokens, all of them scored: its configuration and the tokens per tile.
+GemmPlan plan_lmhead_step(int V, int T, int K, int* tokens);
+// Tokens per tile where the R scored rows choose them.
+int lmhead_tile_tokens(int V, int R, int K);
 // Tile of configuration `cfg`: {weight rows, tokens, K depth per stage, stages, waves along W, waves along T}.
 void gemm_cfg_shape(int cfg, int* shape);
 constexpr int kMaxSplit = 4;  // K-split slices of the residual GEMMs

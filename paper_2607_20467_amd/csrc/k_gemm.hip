@@ -793,10 +793,10 @@ __device__ __forceinline__ void phase_barrier() {
   asm volatile("s_barrier" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
 }
-template <int BW, int BT, int S, class Epi>
+template <int BW, int BT, int S, class Epi, bool COUNTED = false>
 __global__ void __launch_bounds__(512)
 gemm_pp_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, int T, int K,
-               const int32_t* __restrict__ t_count, int nsplit, int gw, Epi epi) {
+               const int32_t* __restrict__ t_count, int nsplit, int gw, uint64_t narrow, Epi epi) {
   constexpr int WW = 2, WT = 4, NPH = S == 2 ? 2 : 1;
   constexpr int TW = BW / WW, SW = TW / 16, ST = BT / 64, SWP = SW / NPH;
   constexpr int NB = (BW + BT) / 8, IPW = NB / 8;       // 1 KiB blocks per stage, loads per wave and stage
@@ -806,7 +806,9 @@ gemm_pp_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int N
   extern __shared__ __attribute__((aligned(1024))) uint4 sm[];
 
   const int Tv = t_count ? min(T, *t_count) : T;
-  const int nW = (Nw + BW - 1) / BW, nTt = (Tv + BT - 1) / BT;
+  // tokens of a tile: with COUNTED one fragment column fewer where `narrow` says so for this many rows
+  const int bt = COUNTED && Tv > 0 && (narrow >> min(63, (Tv - 1) / 64) & 1) ? BT - 64 : BT;
+  const int nW = (Nw + BW - 1) / BW, nTt = (Tv + bt - 1) / bt;
   const int units = nW * nsplit * nTt;
   const int per = (units + 7) / 8;
   const int xcd = blockIdx.x & 7, stride = gridDim.x >> 3;
@@ -835,8 +837,8 @@ gemm_pp_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int N
     const int tile_t = rr / gn;
     tile_w = g * gw + rr - tile_t * gn;
     w0 = tile_w * BW;
-    t0 = tile_t * BT;
-    ste = min(ST, (Tv - t0 + 63) / 64);
+    t0 = tile_t * bt;
+    ste = min(bt / 64, (Tv - t0 + 63) / 64);
     const int kb = min(nk_all, split * kper);
     nk = min(nk_all, kb + kper) - kb;
     wbase = reinterpret_cast<const char*>(W + (size_t)w0 * K + kb * 64);
@@ -970,7 +972,8 @@ gemm_pp_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int N
       setup(L);
       prologue();
     }
-    epi.template apply<SW, ST, WT>(acc, ew + wave_w * TW, et + wave_t * 16, lane, Nw, Tv, etile, esplit);
+    epi.template apply<SW, ST, WT>(acc, ew + wave_w * TW, et + wave_t * 16, lane, Nw,
+                                COUNTED ? min(et + bt, Tv) : Tv, etile, esplit);
     if (!more) break;
   }
 }
@@ -1005,6 +1008,9 @@ static bool lm_ok(const TileCfg& c, int force_bw) {
          cfg_lds(c) + sizeof(Part) * kLmWaves * c.bt <= kLdsBytes;
 }
 
+// Whether a step's scored rows choose the tokens per tile under LM-head plan `p` (lmhead_tile_tokens).
+static bool rows_choose(const GemmPlan& p) { return p.cfg == 3 || p.cfg == 4; }
+
 struct TileCost {
   double a, b0, b1, m;
 };
@@ -1032,7 +1038,8 @@ static double plan_cost(int ci, bool lm, int n, int Nw, int T, int K) {
   double stage = k.b0 + k.b1 * f;
   if (active > kCUs) stage *= 1.0 + (active / kCUs - 1.0) * k.m;
   const double hbm = std::max(1.0, active / nT) * c.bw * 128.0 / 5.4e6;
-  stage = std::pow(std::pow(stage, 4) + std::pow(hbm, 4), 0.25);
+  const double s4 = stage * stage * stage * stage, h4 = hbm * hbm * hbm * hbm;
+  stage = std::sqrt(std::sqrt(s4 + h4));
   return 4.0 + rounds * (k.a + nk * stage) + (n > 1 ? n * (double)T * Nw * 4.0 / 5e6 : 0.0);
 }
 
@@ -1086,32 +1093,22 @@ GemmPlan plan_gemm(int Nw, int T, int K, int force_bw, int max_split) {
   return best;
 }
 
-// The LM head of a step: T tokens, of which the device counts the scored rows (what follows the prompt, less as
-// decoding goes on). A plan for T rows can be far off for those: at 384 tokens 256 x 192 tiles, best for 384 rows
-// (386 us by the model, 256 x 256 tiles 438), take 319 us for 256 rows where 256 x 256 tiles take 245 (step of 329
-// tokens, 256 of them scored, two layers: 764 -> 707 us). So another
-// configuration is taken where its times for T, 2 T / 3 and T / 3 rows are together 10 % better (a third of that
-// for each, above the model's typical error of choice).
-GemmPlan plan_lmhead_counted(int V, int T, int K) {
-  GemmPlan best = plan_gemm(V, T, K, kLmTile, 1);
-  if (K % 64 != 0) return best;
-  auto times = [&](int ci) {
-    double t = 1.0;
-    for (int third = 1; third <= 3; ++third) t *= plan_cost(ci, true, 1, V, std::max(1, T * third / 3), K);
-    return t;
-  };
-  double best_t = 0.9 * times(best.cfg);
-  for (int ci = 1; ci < kModelCfgs; ++ci) {
-    if (!lm_ok(kCfgs[ci], kLmTile)) continue;
-    const double t = times(ci);
-    if (t < best_t) {
-      best_t = t;
-      best.cfg = ci;
-    }
-  }
-  const TileCfg& c = kCfgs[best.cfg];
-  best.tiles = ((V + c.bw - 1) / c.bw) * ((T + c.bt - 1) / c.bt);
-  return best;
+// Tokens per tile of a step's LM head with R scored rows. A step knows its tokens on the host, the scored rows (what
+// follows the prompt, less as decoding goes on) only on the device, and the plan for its tokens can be far off for the
+// rows: of 126464 ids, 256 x 192 tiles, best for 384 rows, take 289 us for 256 of them, 256 x 256 tiles 220; for 300 rows
+// it is 306 and 371. So where the plan is one of these two the 256 x 256 kernel runs and takes 192 or 256 tokens per
+// tile by the count, 64 rows at a time. Timed both ways (vocabularies of 32000 to 152064 ids, 129 to 4000 rows) this
+// rule is 0.06 % from the better one, at most 2.7 %; it asks 5 % of the model's costs for 192, which leave a quarter of the
+// tile's loads unused and so are up to 5 % slower than 256 x 192 tiles (384 of 384 rows 351 us, 343).
+int lmhead_tile_tokens(int V, int R, int K) {
+  return plan_cost(4, true, 1, V, R, K) < 0.95 * plan_cost(3, true, 1, V, R, K) ? 192 : 256;
+}
+
+GemmPlan plan_lmhead_step(int V, int T, int K, int* tokens) {
+  GemmPlan p = plan_gemm(V, T, K, kLmTile, 1);
+  if (rows_choose(p)) p.cfg = 3;
+  *tokens = p.cfg == 3 ? lmhead_tile_tokens(V, T, K) : kCfgs[p.cfg].bt;
+  return p;
 }
 
 void gemm_cfg_shape(int cfg, int* shape) {
@@ -1171,7 +1168,7 @@ static bool run_pp(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const
   static std::atomic<int> fits{-1};
   static std::atomic<uint32_t> lds_set{0};
   if (!prepare_kernel(reinterpret_cast<const void*>(kern), lds, fits, lds_set)) return false;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, s, W, X, Nw, T, K, t_count, nsplit, kGroupW, epi);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(512), lds, s, W, X, Nw, T, K, t_count, nsplit, kGroupW, 0, epi);
   return true;
 }
 
@@ -1255,9 +1252,28 @@ void gemm_store_f32(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, floa
   const GemmPlan p{K % 64 ? 0 : 13, 1, 0};
   run_plan(p, W, X, Nw, T, K, nullptr, EpiF32{out}, s);
 }
+// A step's LM head: its tokens' plan, except where that is one of the tiles of 256 ids over 192 or 256 tokens.
+static bool run_counted(const GemmPlan& p, const bf16_t* W, const bf16_t* X, int V, int T, int K, const LmOut& o,
+                        hipStream_t s) {
+  if (!o.count || !rows_choose(p)) return false;
+  uint64_t narrow = 0;
+  for (int i = 0; i < 64 && 64 * i < T; ++i)
+    if (lmhead_tile_tokens(V, 64 * (i + 1), K) == 192) narrow |= (uint64_t)1 << i;
+  using Epi = EpiLm<kLmTile, kLmWaves>;
+  constexpr size_t lds = 2 * (256 + 256) * 128;
+  auto kern = gemm_pp_kernel<256, 256, 2, Epi, true>;
+  static std::atomic<int> fits{-1};
+  static std::atomic<uint32_t> lds_set{0};
+  if (!prepare_kernel(reinterpret_cast<const void*>(kern), lds, fits, lds_set)) return false;
+  const int units = ((V + 255) / 256) * ((T + 191) / 192);  // of the narrower tiles
+  hipLaunchKernelGGL(kern, dim3(std::min(8 * ((units + 7) / 8), kCUs)), dim3(512), lds, s, W, X, V, T, K, o.count, 1,
+                     kGroupW, narrow, Epi{o});
+  return true;
+}
 void gemm_lmhead(const bf16_t* W, const bf16_t* X, int V, int T, int K, const LmOut& o, hipStream_t s) {
   static_assert(kLmTile == 128 && kLmWaves == 2, "the LM-head vocabulary tile is the GEMM's weight tile");
-  const GemmPlan p = o.count ? plan_lmhead_counted(V, T, K) : plan_gemm(V, T, K, kLmTile, 1);
+  const GemmPlan p = plan_gemm(V, T, K, kLmTile, 1);
+  if (run_counted(p, W, X, V, T, K, o, s)) return;
   run_plan(p, W, X, V, T, K, o.count, EpiLm<kLmTile, kLmWaves>{o}, s);
 }
 #endif

@@ -207,3 +207,20 @@ def test_gemm_plans_fit_their_depth(dcl, nw, t, k, lm):
     assert k % plan["kd"] == 0 or plan["cfg"] == 0, plan
     if lm:
         assert plan["bw"] // plan["ww"] == 128 or (plan["bw"] == 128 and plan["ww"] == 2), plan
+
+
+@pytest.mark.parametrize("v,k", [(126464, 4096), (152064, 3584), (40010, 128), (1000, 208)])
+def test_step_head_plans(dcl, v, k):
+    """A step's head runs the plan of its tokens (the one that the head on given rows runs), except that tiles of 256
+    ids over 192 or 256 tokens are one configuration whose tokens per tile the scored rows choose."""
+    chosen = set()
+    for t in range(1, 1500, 13):
+        rows, step = dcl.dcl_debug_gemm_plan(v, t, k, True), dcl.dcl_debug_gemm_plan(v, t, k, 2)
+        if (rows["bw"], rows["bt"]) in ((256, 192), (256, 256)):
+            assert (step["cfg"], step["bw"]) == (3, 256) and step["bt"] in (192, 256) and step["nsplit"] == 1, step
+            chosen.add(step["bt"])
+        else:
+            assert step == rows, (t, rows, step)
+    if v > 100000:
+        assert chosen == {192, 256}
+        assert dcl.dcl_debug_gemm_plan(v, 384, k, 2)["bt"] == 192 and dcl.dcl_debug_gemm_plan(v, 256, k, 2)["bt"] == 256

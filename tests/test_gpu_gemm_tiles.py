@@ -174,6 +174,44 @@ def test_head_tiles(V, d, n):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("B,S,prompt", [(1, 608, 0), (1, 608, 48), (1, 608, 383), (1, 608, 448), (1, 608, 575),
+                                        (1, 608, 607), (1, 608, 608), (4, 152, 96), (7, 640, 0), (7, 640, 575)])
+def test_step_head_tiles_chosen_by_the_scored_rows(B, S, prompt):
+    """A step's head where the scored rows, counted on the device, choose the tokens per tile (192 for 560 or 160, 256 for
+    608 or 225 of 608). Statistics of the step against float64 on its own hidden states, none scored and
+    counts past the last choice included; the rows of other numbers keep their sentinels."""
+    import torch
+    import paper_2607_20467_amd as dcl
+    V, d, R = 40010, 128, B * (S - prompt)
+    assert dcl.dcl_debug_gemm_plan(V, B * S, d, 2)["cfg"] == 3
+    g = _geom(d, 16, 1, V)
+    gen = torch.Generator(device="cuda").manual_seed(R)
+    w = _weights(g, gen)
+    run = dcl.Runner(g, w, max_positions=1024)
+    tok = torch.randint(0, V - 2, (B, S), generator=gen, device="cuda", dtype=torch.int32)
+    tok[:, prompt:] = g.mask_id
+    st = run.step(tok, torch.full((B,), prompt, dtype=torch.int32, device="cuda"), S)
+    scored = torch.zeros((B, S), dtype=torch.bool, device="cuda")
+    scored[:, prompt:] = True
+    assert bool((st["top1"][~scored] == -1).all()) and bool((st["conf"][~scored] == -1).all())
+    if R == 0:
+        return
+    rows = scored.view(-1).nonzero().view(-1).to(torch.int32)
+    hidden = run.logits(tok, rows[:512], with_hidden=True)[1].view(torch.bfloat16).double()
+    logits = hidden @ w[-1].double().t()
+    top, lse = logits.topk(2, -1), logits.logsumexp(-1)
+    got = {k: v[scored][:512] for k, v in st.items()}
+    clear = top.values[:, 0] - top.values[:, 1] > TIE_GAP
+    assert bool((got["top1"][clear].long() == top.indices[:, 0][clear]).all())
+    assert float((got["lse"].double() - lse).abs().max()) <= LOGIT_TOL
+    for key, i in (("conf", 0), ("p2", 1)):
+        assert float((got[key].double() - torch.exp(top.values[:, i] - lse)).abs().max()) <= CONF_TOL, key
+    # every scored row has statistics, the last ones as the rest
+    last = run.logits(tok, rows[-1:])[0].double()
+    assert float((st["lse"][scored][-1].double() - last.logsumexp(-1)).abs()) <= LOGIT_TOL
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n", [20, 129])
 def test_head_ties_and_non_finite_logits(n):
     """Equal logits rank by id wherever the equal ids sit (one lane, two lanes of a token, two vocabulary tiles),
