@@ -408,34 +408,40 @@ static void run_attn(const AttnArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(kern, grid, dim3(NQ * KG * 64), lds, s, a);
 }
 
-// Rings of two steps; 32-key tiles (64-key tiles and deeper rings were slower at every size). The layout follows from
-// the query waves (16 queries each) that the call has, over 256 CUs of four SIMDs. Kernel alone, K / V warm, us,
-// against 4 query waves x 2 key groups of 16 queries (8 x 1 from 4096 query waves on), the two layouts in use before:
-//   up to 256: a workgroup per query wave whose four waves share out the keys: otherwise few CUs have work at all.
-//     32 (1 x 16 tokens over 1900 keys) 39.2 -> 25.1, 128 (1 x 64 over 323) 12.8 -> 9.8, head_dim 64, 24 (1 x 96) 4.8 -> 3.8
+// Rings of two steps. The layout follows from the query waves (16 queries each) that the call has and from how its
+// workgroups fill 256 CUs of four SIMDs, which hold two (layouts of 2 x 2 waves) or three (4 x 1 x 1) of them. Kernel
+// in the layer, us, cached keys from HBM, against other layouts:
+//   up to 256 query waves: a workgroup per query wave whose four waves share out the keys: otherwise few CUs have work
+//     at all. 32 (1 x 16 tokens over 1900 keys, kernel alone) 39.2 -> 25.1, head_dim 64, 24 (1 x 96) 4.8 -> 3.8
 //     (up to 64 keys most of those waves would have none: the next layout, 2 - 7 % faster there)
-//   up to 640, without a cache 800: 32-query workgroups, so more CUs have one: 448 (4 x 64 over 1000) 1.39 times as
-//     fast, 768 (1 x 384) 12.9 -> 12.2; with a cache every workgroup more reads it once more (768, 8 x 40 over 2000:
-//     17 % slower than before)
+//   up to 640, without a cache 1024: 32-query workgroups, so more CUs have one: 896 (1 x 448) 16.6 -> 16.2, Dream's (1 x
+//     512) 18.5 -> 17.6; with a cache every workgroup more reads it once more (1024, 8 x 64 over 1216: 10 % slower)
 //   few keys: one key group, since a group's share would be one to five tiles and the merge: 1092 (3 x 203) 14.7 -> 13.3
-//   up to 2048: two query fragments per wave and two key groups (1024, 8 x 64 over 1216, 37.3 -> 36.5; 1472, 1 x 730,
-//     31.5 -> 30.5); up to 2800 workgroups of 64 queries, four to a CU, even out the last round (2432, 2 x 600, 41.2 ->
-//     37.4; 2624, 1 x 1300, 78.2 -> 73.3); above, 128 (3648, 2 x 900, 76.0 -> 66.8; 5376, 4 x 768, 82.2 -> 80.2).
-// Over 310 sizes of 16 to 3072 tokens and 0 to 2000 cached keys the rule is on average 2 % slower than the fastest
-// layout of each, the two layouts before 21 %.
+//   up to 512 workgroups of 64 queries, two to a CU: two query fragments per wave and two key groups (2048, 1 x 1024,
+//     40.7 -> 38.2); up to 768, three to a CU: one fragment, one group (2624, 1 x 1300, 78.2 -> 73.3; 3072, 1 x 1536, 86.4 ->
+//     78.8; 4 x 384 30.2 -> 27.2); above, 128 queries (3616, 1 x 1800, 1.15 times as fast as 64).
+// head_dim 64: 64-key tiles halve the steps of four query waves x two key groups, which is the faster layout over more
+// than 320 keys where 129 to 256 or 385 to 512 of its workgroups fill one round of the CUs, or more than 640 the last one
+// (1024, 1 x 1024, 20.0 -> 18.7; 2048, 1 x 2048, 48.9 -> 43.9; 3072, 4 x 768, 32.1 -> 29.5); in between 32-query
+// workgroups are (1280, 1 x 1280, 1.10 times as fast).
+// Over 331 sizes (4 to 32 heads, 16 to 3072 tokens, 0 to 2003 cached keys) the rule is on average 0.6 % slower than the
+// fastest of eight layouts, at most 12 % (2304 to 2560 tokens of 28 or 32 heads).
 void launch_attention(const AttnArgs& a, hipStream_t s) {
-  const long query_waves = (long)a.B * a.H * ((a.S + 15) / 16);
+  const long query_waves = (long)a.B * a.H * ((a.S + 15) / 16), wg64 = (long)a.B * a.H * ((a.S + 63) / 64);
   const int nkeys = a.P + (a.Sk ? a.Sk : a.S);
   const bool few = query_waves <= 256 && nkeys > 64;
   if (a.dh == 128) {
     if (few) run_attn<1, 1, 4, 32, 128, 2>(a, s);
-    else if (query_waves > 640 && query_waves <= 2800 && (nkeys <= 320 || query_waves >= 2048))
+    else if (query_waves > 640 && (query_waves <= 2800 || wg64 <= 768) &&
+             (nkeys <= 320 || (query_waves >= 2048 && wg64 > 512)))
       run_attn<4, 1, 1, 32, 128, 2>(a, s);
-    else if (query_waves <= (a.P ? 640 : 800)) run_attn<2, 1, 2, 32, 128, 2>(a, s);
-    else if (query_waves < 2048) run_attn<2, 2, 2, 32, 128, 2>(a, s);
+    else if (query_waves <= (a.P ? 640 : 1024)) run_attn<2, 1, 2, 32, 128, 2>(a, s);
+    else if (query_waves < 2048 || wg64 <= 512) run_attn<2, 2, 2, 32, 128, 2>(a, s);
     else run_attn<4, 2, 1, 32, 128, 2>(a, s);
   } else {
+    const bool filled = wg64 <= 256 ? wg64 > 128 : wg64 <= 512 ? wg64 > 384 : wg64 > 640;
     if (few) run_attn<1, 1, 4, 32, 64, 2>(a, s);
+    else if (nkeys > 320 && filled) run_attn<4, 1, 2, 64, 64, 2>(a, s);
     else run_attn<2, 1, 2, 32, 64, 2>(a, s);
   }
 }
