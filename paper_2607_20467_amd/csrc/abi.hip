@@ -777,7 +777,8 @@ static ScoreLayout score_layout(const dcl_config& c, int n) {
     return o;
   };
   L.n_vt = (c.vocab + kLmTile - 1) / kLmTile;
-  take((size_t)n * 4);  // a row map and its count once stood here; the size is what callers allocate
+  // Unused: callers may have stored the size that dcl_score_workspace_bytes gave them, so it does not shrink or grow.
+  take((size_t)n * 4);
   take(4);
   const size_t np = (size_t)n * L.n_vt * 4;
   L.pm1 = take(np);

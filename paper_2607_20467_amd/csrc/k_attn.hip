@@ -417,9 +417,9 @@ static void run_attn(const AttnArgs& a, hipStream_t s) {
 //   up to 640, without a cache 1024: 32-query workgroups, so more CUs have one: 896 (1 x 448) 16.6 -> 16.2, Dream's (1 x
 //     512) 18.5 -> 17.6; with a cache every workgroup more reads it once more (1024, 8 x 64 over 1216: 10 % slower)
 //   few keys: one key group, since a group's share would be one to five tiles and the merge: 1092 (3 x 203) 14.7 -> 13.3
-//   up to 512 workgroups of 64 queries, two to a CU: two query fragments per wave and two key groups (2048, 1 x 1024,
-//     40.7 -> 38.2); up to 768, three to a CU: one fragment, one group (2624, 1 x 1300, 78.2 -> 73.3; 3072, 1 x 1536, 86.4 ->
-//     78.8; 4 x 384 30.2 -> 27.2); above, 128 queries (3616, 1 x 1800, 1.15 times as fast as 64).
+//   up to 512 workgroups of 64 queries, two to a CU: two query fragments per wave and two key groups (2048, 1 x
+//     1024, 40.7 -> 38.2); up to 768, three to a CU: one fragment, one group (2624, 1 x 1300, 78.2 -> 73.3; 3072, 1 x
+//     1536, 86.4 -> 78.8; 4 x 384 30.2 -> 27.2); above, 128 queries (3616, 1 x 1800, 1.15 times as fast as 64).
 // head_dim 64: 64-key tiles halve the steps of four query waves x two key groups, which is the faster layout over more
 // than 320 keys where 129 to 256 or 385 to 512 of its workgroups fill one round of the CUs, or more than 640 the last one
 // (1024, 1 x 1024, 20.0 -> 18.7; 2048, 1 x 2048, 48.9 -> 43.9; 3072, 4 x 768, 32.1 -> 29.5); in between 32-query

@@ -14,8 +14,9 @@
 //   PARTIAL float32 split-K slice, folded into the residual stream by the next RMSNorm;
 //   F32    plain float32 store (debug logits).
 // Tiles: BW weight rows x BT tokens per workgroup, K staged through a multi-stage LDS ring of 64-deep
-// slices filled by direct-to-LDS DMA. Two kernels: gemm_pp_kernel, whose two waves per SIMD alternate
-// between reading and multiplying (the large tiles), and gemm_kernel (few tokens, K tails). The unit ->
+// slices (128-deep for at most 64 tokens) filled by direct-to-LDS DMA. Two kernels: gemm_pp_kernel, whose two
+// waves per SIMD alternate between reading and multiplying (the large tiles), and gemm_kernel (few tokens, K
+// tails, and two tiles of one round of units). The unit ->
 // workgroup map is XCD-aware: tiles that share operands land on the same XCD and its L2. The
 // configuration comes from a cost model with measured constants per configuration (gemm_tuned.inc).
 #include <float.h>
@@ -66,7 +67,8 @@ struct EpiResid {
 // g / (1 + e^-g): the quotient by reciprocal and one correction step (exact remainder), at two thirds of the IEEE
 // division's instructions. It is within an ulp of that where the denominator is below 2^126 (g > -87.3; past it the
 // reciprocal and the remainder leave the normal range) and g is finite (the correction of inf is NaN). `range` adds up
-// the denominators, and a correction that is not finite makes it NaN: with range < 2^126 every quotient it has seen holds.
+// the denominators, and a correction that is not finite makes it NaN: with range < 2^126 every quotient that it has
+// seen holds.
 constexpr float kSiluRange = 0x1p126f;
 __device__ __forceinline__ float silu(float g, float& range) {
   const float x = 1.0f + __expf(-g);
@@ -381,8 +383,9 @@ __device__ __forceinline__ float pair_lanes(float v, bool far, Op op) {
 // over the four lanes of the token, then the sums relative to the wave's top-1 value. VALU-bound: about 7
 // operations a value for the top two with their ids and 8 for the sums (the exponential counts 4), against
 // about 28 with ties, the vocabulary's end and the left-out id tested per value (the general version below):
-// 126464 x 4096 at 32 / 256 rows 202 -> 183 / 266 -> 251 us, 152064 x 3584 at 1920 rows 1850 -> 1707 us. Returns false where a value is not finite enough for the short cuts
-// (NaN, infinities, fewer than two values above -inf); the general version then gives that fragment.
+// 126464 x 4096 at 32 / 256 rows 202 -> 183 / 266 -> 251 us, 152064 x 3584 at 1920 rows 1850 -> 1707 us. Returns
+// false where a value is not finite enough for the short cuts (NaN, infinities, fewer than two values above -inf); the
+// general version then gives that fragment.
 template <int SW, int ST>
 __device__ __forceinline__ bool lm_fragment(const f32x4_t (&acc)[SW][ST], int j, int wq, Part& p) {
   float m1 = fmaxf(acc[0][j][0], acc[0][j][1]), m2 = fminf(acc[0][j][0], acc[0][j][1]);
@@ -1011,6 +1014,9 @@ static bool lm_ok(const TileCfg& c, int force_bw) {
 // Whether a step's scored rows choose the tokens per tile under LM-head plan `p` (lmhead_tile_tokens).
 static bool rows_choose(const GemmPlan& p) { return p.cfg == 3 || p.cfg == 4; }
 
+// Configurations of the LM head alone (256 x 64, 128 x 64).
+static constexpr bool lm_only(int ci) { return ci == 6 || ci == 14; }
+
 struct TileCost {
   double a, b0, b1, m;
 };
@@ -1043,7 +1049,7 @@ static double plan_cost(int ci, bool lm, int n, int Nw, int T, int K) {
   return 4.0 + rounds * (k.a + nk * stage) + (n > 1 ? n * (double)T * Nw * 4.0 / 5e6 : 0.0);
 }
 
-#if !defined(DCL_GEMM_PART) || DCL_GEMM_PART == 1
+#if DCL_GEMM_PART == 1
 // At most 64 tokens without a K split: the time is that of streaming the weights, and what decides it is how evenly
 // the CUs share them and how much each has in flight, so the smallest tile whose units fit one round of the CUs is
 // taken, with 128-deep stages (256 contiguous bytes of each weight row per load) filling the LDS. Against the
@@ -1070,9 +1076,10 @@ GemmPlan plan_gemm(int Nw, int T, int K, int force_bw, int max_split) {
   for (int ci = 0; sc < 0 && ci < kModelCfgs; ++ci) {
     // K not a multiple of the stage depth: one tail-aware configuration (128 x 128, 64-deep stages, which also
     // suits the LM head's split layout) serves every such shape, so the others carry no tail handling. It is
-    // the slower kernel everywhere else; 128 x 64 tiles pay only under the LM head (they halve the last round).
+    // the slower kernel everywhere else; 256 x 64 and 128 x 64 tiles pay only under the LM head (they halve the last
+    // round).
     if ((K % kCfgs[ci].kd != 0) != (ci == 0)) continue;
-    if (ci == kModelCfgs - 1 && !lm) continue;
+    if (!lm && lm_only(ci)) continue;
     if (!lm_ok(kCfgs[ci], force_bw)) continue;
     for (int n = 1; n <= max_split && (n == 1 || (n - 1) * ((nk + n - 1) / n) < nk); ++n) {
       const double t = plan_cost(ci, lm, n, Nw, T, K);
@@ -1094,12 +1101,12 @@ GemmPlan plan_gemm(int Nw, int T, int K, int force_bw, int max_split) {
 }
 
 // Tokens per tile of a step's LM head with R scored rows. A step knows its tokens on the host, the scored rows (what
-// follows the prompt, less as decoding goes on) only on the device, and the plan for its tokens can be far off for the
-// rows: of 126464 ids, 256 x 192 tiles, best for 384 rows, take 289 us for 256 of them, 256 x 256 tiles 220; for 300 rows
+// follows the prompt, less as decoding goes on) only on the device, and the plan for its tokens can be far off for
+// the rows: of 126464 ids, 256 x 192 tiles, best for 384 rows, take 289 us for 256 of them, 256 x 256 tiles 220; for 300 rows
 // it is 306 and 371. So where the plan is one of these two the 256 x 256 kernel runs and takes 192 or 256 tokens per
 // tile by the count, 64 rows at a time. Timed both ways (vocabularies of 32000 to 152064 ids, 129 to 4000 rows) this
-// rule is 0.06 % from the better one, at most 2.7 %; it asks 5 % of the model's costs for 192, which leave a quarter of the
-// tile's loads unused and so are up to 5 % slower than 256 x 192 tiles (384 of 384 rows 351 us, 343).
+// rule is 0.06 % from the better one, at most 2.7 %; it asks 5 % of the model's costs for 192, which leave a quarter
+// of the tile's loads unused and so are up to 7 % slower than 256 x 192 tiles (384 of 384 rows 351 us, 343).
 int lmhead_tile_tokens(int V, int R, int K) {
   return plan_cost(4, true, 1, V, R, K) < 0.95 * plan_cost(3, true, 1, V, R, K) ? 192 : 256;
 }
@@ -1175,12 +1182,12 @@ static bool run_pp(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const
 static_assert(kNumCfgs == 20, "run_plan dispatches every configuration of kCfgs");
 
 // Whether the epilogue has a kernel for configuration CI: the LM head runs only the layouts of lm_ok, the debug
-// logits (test support) one tile, 128 x 64 tiles serve only the LM head and the 128 x 192 ring only residual GEMMs.
+// logits (test support) one tile, and the 128 x 192 ring serves only residual GEMMs.
 template <class Epi, int CI>
 constexpr bool has_cfg() {
   if (Epi::kKind == kEpiLm) return (CI >= 3 && CI <= 6) || CI == 11 || CI == 13 || CI == 14;
   if (Epi::kKind == kEpiDebug) return CI == 13;
-  return CI != 14 && (CI != 19 || Epi::kKind == kEpiResid);
+  return !lm_only(CI) && (CI != 19 || Epi::kKind == kEpiResid);
 }
 
 template <class Epi>
@@ -1222,18 +1229,13 @@ static void run_plan(const GemmPlan& p, const bf16_t* W, const bf16_t* X, int Nw
   if (!ok) run_cfg<128, 128, 64, 2, 2, 4, Epi, true>(W, X, Nw, T, K, t_count, n, epi, s);
 }
 
-// The wrappers below are compiled as three objects (DCL_GEMM_PART 1-3, in parallel), or all at once.
-#ifndef DCL_GEMM_PART
-#define DCL_GEMM_PART 0
-#endif
-#define DCL_PART(n) (DCL_GEMM_PART == 0 || DCL_GEMM_PART == n)
-
-#if DCL_PART(1)
+// The wrappers below are compiled as three objects (DCL_GEMM_PART 1-3, in parallel).
+#if DCL_GEMM_PART == 1
 void gemm_qkv(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const QkvOut& o, hipStream_t s) {
   run_plan(plan_gemm(Nw, T, K, 0, 1), W, X, Nw, T, K, nullptr, EpiQkv{o}, s);
 }
 #endif
-#if DCL_PART(2)
+#if DCL_GEMM_PART == 2
 int gemm_resid(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, float* r, float* P, hipStream_t s) {
   const GemmPlan p = plan_gemm(Nw, T, K, 0, P ? kMaxSplit : 1);
   if (p.nsplit > 1) {
@@ -1244,7 +1246,7 @@ int gemm_resid(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, float* r,
   return 0;
 }
 #endif
-#if DCL_PART(3)
+#if DCL_GEMM_PART == 3
 void gemm_swiglu(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, bf16_t* a, hipStream_t s) {
   run_plan(plan_gemm(Nw, T, K, 0, 1), W, X, Nw, T, K, nullptr, EpiSwiglu{a}, s);
 }

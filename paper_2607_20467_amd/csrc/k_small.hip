@@ -324,7 +324,7 @@ void launch_merge(const float* pm1, const int32_t* pi1, const float* pm2, const 
                        rows, count, max_rows, st);
 }
 
-// rows[j] = j for j < n, count = n (row map of dcl_score_hidden and dcl_debug_logits' copy).
+// rows[j] = j for j < n, count = n (the row count of dcl_debug_logits, whose rows the caller gives).
 __global__ void iota_kernel(int32_t* __restrict__ rows, int32_t* __restrict__ count, int n) {
   int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j < n) rows[j] = j;
