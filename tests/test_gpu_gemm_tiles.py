@@ -22,7 +22,10 @@ LAYERS = [(384, 6144, 4, 17), (384, 6144, 4, 129), (384, 6144, 4, 200), (384, 61
           # one token tile (32 x 32 tiles; 32, 48 and 96 rows x 64 tokens): remainders of rows and tokens, short K
           (128, 6144, 4, 33), (128, 4160, 4, 63), (128, 8000, 4, 64), (256, 2000, 4, 31), (1408, 304, 12, 1)]
 HEADS = [(1000, 256, 1), (5003, 256, 63), (40001, 128, 65), (40000, 128, 130), (40010, 128, 200), (20000, 256, 257),
-         (126464, 128, 33), (126464, 128, 64), (5003, 208, 131)]
+         (126464, 128, 33), (126464, 128, 64), (5003, 208, 131),
+         # 128 ids split over two waves, 128 and 256 tokens: several units per workgroup, partly filled columns
+         (152064, 512, 33), (152064, 512, 128), (16010, 512, 193), (32003, 1024, 65),
+         (24001, 2048, 129), (24001, 4096, 600), (16010, 4096, 257), (32003, 2048, 189)]
 
 
 def _plans(dcl):
@@ -41,7 +44,7 @@ def test_shapes_cover_every_configuration():
     layer, head = _plans(dcl)
     want = set(range(20)) - {6, 14}
     assert layer >= want, f"configurations {sorted(want - layer)} not covered"
-    assert head >= {0, 3, 4, 5, 6, 14}, f"head configurations covered: {sorted(head)}"
+    assert head >= {0, 3, 4, 5, 6, 11, 13, 14}, f"head configurations covered: {sorted(head)}"
 
 
 def _geom(d, F, H, V=512):
