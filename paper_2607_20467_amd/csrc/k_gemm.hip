@@ -308,7 +308,7 @@ struct EpiF32 {
 };
 
 // Split-K slice: unit `split` writes its float32 partial C to P + split * stride ([T, Nw] each);
-// the consumer (the next RMSNorm) adds the slices to the residual stream in split order.
+// the consumer (the next RMSNorm) adds the slices up in split order and the sum to the residual stream.
 struct EpiPartial {
   float* P;
   size_t stride;
