@@ -261,7 +261,7 @@ struct EpiQkv {
   // of every k and v^T row of a sequence. The wave that holds a sequence's first token copies the elements of its
   // own weight rows, one per lane and step (up to 7 for each row). As a launch of its own this copy took 4.1 - 4.8 us
   // of each layer (1 x 64 tokens over 323 keys); the QKV launch takes 28.8 us with it, on tiles that take 24.3 alone
-  // with a plain epilogue (26.4 and 30.3 on the tiles of before, without the copy).
+  // with a plain epilogue (64 x 64 tiles without the copy: 30.3 and 26.4).
   template <int SW, int ST, int JS>
   __device__ __forceinline__ void carry(int wb, int tb, int lane, int Nw, int T) const {
     const int DH = o.dh, qrows = o.H * DH, kvrows = o.Hkv * DH;
@@ -790,7 +790,8 @@ gemm_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, 
 // both operands in its L2 (L2 misses limit the fill at thousands of tokens: at gw = 1, 27 % of the
 // requests of the case above miss). A workgroup issues the first stages of its next unit before the epilogue.
 // A partly filled token tile computes only the ceil(valid / 64) token fragments a wave needs: fragment j of
-// wave t is the tokens [64 j + 16 t, +16), so the valid ones spread over all waves.
+// wave t is the tokens [64 j + 16 t, +16), so the valid ones spread over all waves. With COUNTED (a step's LM head) the
+// same serves tiles of one fragment column fewer, where the rows fill those better (lmhead_tile_tokens).
 __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_barrier" ::: "memory");
@@ -1055,7 +1056,7 @@ static double plan_cost(int ci, bool lm, int n, int Nw, int T, int K) {
 // taken, with 128-deep stages (256 contiguous bytes of each weight row per load) filling the LDS. Against the
 // 64 x 64 tiles with 64-deep stages that the cost model picks (weights from HBM, us):
 //   64 tokens: 12288 x 4096 26.4 -> 24.3 (48 rows: 256 units, 64 rows: 192), 24576 x 4096 46.7 -> 43.0 (96 rows),
-//              4608 x 3584 20.0 -> 15.4 (32 rows); the wider tile loses in each (33.5 and 30.4 for 12288 with 32 and 96 rows)
+//              4608 x 3584 20.0 -> 15.4 (32 rows); other widths lose (33.5 and 30.4 for 12288 with 32 and 96 rows)
 //   24 tokens, 32 x 32 tiles (their activations are half the loads): 24.4 -> 23.1, 41.3 -> 36.7, 17.7 -> 11.2
 // More weight rows than 96 x 256 (37888 x 3584 at 24 tokens: 192 x 64 tiles 48.5, 32 x 32 tiles 50.5), and residual
 // GEMMs (four K slices already give 64 x 64 tiles a unit per CU): the cost model.
