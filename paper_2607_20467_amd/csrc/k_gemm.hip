@@ -768,8 +768,8 @@ gemm_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, 
 //
 // What bounds it: in gemm_kernel every wave of a workgroup reads fragments at the same time and then
 // multiplies at the same time, so the LDS port and the matrix pipe take turns (256 x 256 tiles at 3072 x 37888
-// x 3584: MFMA busy 57 % of the cycles at 2.09 GHz). Half a phase apart they overlap: 67 % at 1.92 GHz, where
-// the clock is what the power budget leaves. 662 -> 602 us (1386 TFLOP/s); 24576 x 1280 x 4096: 219 -> 199 us.
+// x 3584: MFMA busy 56 % of the cycles). Half a phase apart they overlap: 69 %, at the clock that the power
+// budget leaves then. In the step 679 -> 581 us (1437 TFLOP/s); 24576 x 1280 x 4096: 208 -> 183 us.
 //
 // A phase is one 64-deep K stage of all the wave's rows, or (two-stage rings, NPH = 2) half of the rows, so
 // that half a stage's weights can be refilled a phase earlier: the LDS ring is the limit on the bytes in
@@ -787,8 +787,8 @@ gemm_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, 
 //
 // Units as in gemm_kernel, but each XCD's run is walked in groups of `gw` weight tiles, all token tiles of
 // a group in turn (weight tile innermost), so the 32 workgroups of an XCD cover about gw x 8 tiles and share
-// both operands in its L2 (L2 misses limit the fill at thousands of tokens: at gw = 1, 27 % of the
-// requests of the case above miss). A workgroup issues the first stages of its next unit before the epilogue.
+// both operands in its L2 (L2 misses limit the fill at thousands of tokens: of the case above 36 % of the requests
+// miss at gw = 1, 25 % at 4). A workgroup issues the first stages of its next unit before the epilogue.
 // A partly filled token tile computes only the ceil(valid / 64) token fragments a wave needs: fragment j of
 // wave t is the tokens [64 j + 16 t, +16), so the valid ones spread over all waves. With COUNTED (a step's LM head) the
 // same serves tiles of one fragment column fewer, where the rows fill those better (lmhead_tile_tokens).
@@ -1043,7 +1043,7 @@ static double plan_cost(int ci, bool lm, int n, int Nw, int T, int K) {
   const double full = c.bt / 64.0, last = c.pp ? (double)((T - (nT - 1) * c.bt + 63) / 64) : full;
   const double f = rounds > 1 ? (full * (nT - 1) + last) / nT : (nT > 1 ? full : last);
   double stage = k.b0 + k.b1 * f;
-  if (active > kCUs) stage *= 1.0 + (active / kCUs - 1.0) * k.m;
+  if (active > kCUs) stage *= 1.0 + (std::ceil(active / kCUs) - 1.0) * k.m;  // the CUs that hold one more set the time
   const double hbm = std::max(1.0, active / nT) * c.bw * 128.0 / 5.4e6;
   const double s4 = stage * stage * stage * stage, h4 = hbm * hbm * hbm * hbm;
   stage = std::sqrt(std::sqrt(s4 + h4));
