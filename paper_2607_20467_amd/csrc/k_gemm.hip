@@ -1058,12 +1058,14 @@ static double plan_cost(int ci, bool lm, int n, int Nw, int T, int K) {
 //   64 tokens: 12288 x 4096 26.4 -> 24.3 (48 rows: 256 units, 64 rows: 192), 24576 x 4096 46.7 -> 43.0 (96 rows),
 //              4608 x 3584 20.0 -> 15.4 (32 rows); other widths lose (33.5 and 30.4 for 12288 with 32 and 96 rows)
 //   24 tokens, 32 x 32 tiles (their activations are half the loads): 24.4 -> 23.1, 41.3 -> 36.7, 17.7 -> 11.2
+//   12289 to 16384 rows: 64 x 64 tiles have the unit per CU (16384 x 2048: 19.3, 96 rows 21.4; 16 tokens 18.6, 32 x 32
+//              tiles 19.9)
 // More weight rows than 96 x 256 (37888 x 3584 at 24 tokens: 192 x 64 tiles 48.5, 32 x 32 tiles 50.5), and residual
 // GEMMs (four K slices already give 64 x 64 tiles a unit per CU): the cost model.
 static int stream_cfg(int Nw, int T, int K) {
   if (T > 64 || K % 128 != 0) return -1;
-  for (int ci = 16; ci <= 18; ++ci)
-    if (Nw <= kCfgs[ci].bw * kCUs) return T <= 32 ? 15 : ci;
+  for (int ci : {16, 17, 1, 18})
+    if (Nw <= kCfgs[ci].bw * kCUs) return ci != 1 && T <= 32 ? 15 : ci;
   return -1;
 }
 

@@ -20,7 +20,7 @@ LAYERS = [(384, 6144, 4, 17), (384, 6144, 4, 129), (384, 6144, 4, 200), (384, 61
           (256, 3072, 4, 700), (1024, 3072, 16, 1025), (1024, 3072, 16, 600), (2048, 3072, 16, 1025),
           (1152, 12288, 2, 497), (400, 208, 4, 131),
           # one token tile (32 x 32 tiles; 32, 48 and 96 rows x 64 tokens): remainders of rows and tokens, short K
-          (128, 6144, 4, 33), (128, 4160, 4, 63), (128, 8000, 4, 64), (256, 2000, 4, 31), (1408, 304, 12, 1)]
+          (128, 6144, 4, 33), (128, 4160, 4, 63), (128, 8000, 4, 64), (128, 8320, 4, 64), (256, 2000, 4, 31), (1408, 304, 12, 1)]
 HEADS = [(1000, 256, 1), (5003, 256, 63), (40001, 128, 65), (40000, 128, 130), (40010, 128, 200), (20000, 256, 257),
          (126464, 128, 33), (126464, 128, 64), (5003, 208, 131),
          # 128 ids split over two waves, 128 and 256 tokens: several units per workgroup, partly filled columns
