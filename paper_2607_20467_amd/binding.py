@@ -365,7 +365,8 @@ def dcl_debug_gemm_plan(Nw: int, T: int, K: int, lm_head: int = False, max_split
     """The tile plan of a GEMM shape (host only): configuration, K-split slices and tile geometry. lm_head: True (1) for
     the head on given rows, 2 for a step's head whose tokens are all scored."""
     info = (ctypes.c_int32 * 8)()
-    _check(load_library().dcl_debug_gemm_plan(Nw, T, K, int(lm_head), max_split, info), "dcl_debug_gemm_plan")
+    lm = 2 if lm_head == 2 else 1 if lm_head else 0
+    _check(load_library().dcl_debug_gemm_plan(Nw, T, K, lm, max_split, info), "dcl_debug_gemm_plan")
     keys = ("cfg", "nsplit", "bw", "bt", "kd", "stages", "ww", "wt")
     return dict(zip(keys, list(info)))
 
