@@ -39,7 +39,7 @@ __device__ __forceinline__ f32x4_t mfma16(const bf16x8_t& a, const bf16x8_t& b, 
 // apply(): acc[i][j] holds C[wb + 16 i + 4 (lane/16) + r][tb + 16 JS j + lane%16], r = 0..3 (JS: the stride
 // of a wave's token fragments, in fragments).
 
-enum { kEpiPlain, kEpiResid, kEpiLm, kEpiDebug };
+enum { kEpiPlain, kEpiQkv, kEpiResid, kEpiLm, kEpiDebug };
 
 struct EpiResid {
   float* r;
@@ -148,7 +148,7 @@ struct EpiSwiglu {
 // Offsets are 32-bit element counts: gemm_qkv rejects outputs of 2^31 elements or more.
 struct EpiQkv {
   QkvOut o;
-  static constexpr int kKind = kEpiPlain;
+  static constexpr int kKind = kEpiQkv;
   template <int SW, int ST, int JS = 1>
   __device__ __forceinline__ void apply(f32x4_t (&acc)[SW][ST], int wb, int tb, int lane, int Nw, int T, int, int) const {
     const int DH = o.dh, HALF = DH >> 1, LOG2DH = DH == 128 ? 7 : 6;  // head_dim 64 or 128
@@ -255,33 +255,45 @@ struct EpiQkv {
       }
       if constexpr (SW % 2) single(SW - 1);
     }
-    if (o.kc) carry<SW, ST, JS>(wb, tb, lane, Nw, T);
   }
   // A ragged cached prefix: the koff newest cached keys and values go in front of the fresh ones, slots [0, koff)
-  // of every k and v^T row of a sequence. The wave that holds a sequence's first token copies the elements of its
-  // own weight rows, one per lane and step (up to 7 for each row). As a launch of its own this copy took 4.1 - 4.8 us
-  // of each layer (1 x 64 tokens over 323 keys); the QKV launch takes 28.8 us with it, on tiles that take 24.3 alone
-  // with a plain epilogue (64 x 64 tiles without the copy: 30.3 and 26.4).
-  template <int SW, int ST, int JS>
-  __device__ __forceinline__ void carry(int wb, int tb, int lane, int Nw, int T) const {
-    const int DH = o.dh, qrows = o.H * DH, kvrows = o.Hkv * DH;
-    const int w_lo = max(wb, qrows), n = (min(wb + 16 * SW, Nw) - w_lo) * o.koff;
-    for (int j = 0; j < ST; ++j) {
-      const int t0 = tb + 16 * JS * j;
-      for (int b = (t0 + o.S - 1) / o.S; b * o.S < min(t0 + 16, T); ++b) {
-#pragma unroll 4
-        for (int e = lane; e < n; e += 64) {
-          const int x = e / o.koff, z = e - x * o.koff, w = w_lo + x - qrows;  // row of k, then of v^T
-          const int key = o.pos0 - o.koff + z;
-          if (w < kvrows) {  // pairs of rows are dimensions jp and jp + DH / 2
-            const int head = b * o.Hkv + w / DH, wl = w & (DH - 1), d = (wl >> 1) + (wl & 1) * (DH >> 1);
-            o.k[((size_t)head * o.Sk + z) * DH + d] = o.kc[((size_t)head * o.Pc + key) * DH + d];
-          } else {
-            const size_t row = (size_t)b * kvrows + (w - kvrows);
-            o.vt[row * o.Sp + z] = o.vc[row * o.Pc + key];
-          }
-        }
+  // of every k and v^T row of a sequence. The workgroup whose tile holds a sequence's first token copies the rows of
+  // its weight rows, one row per thread with all its loads in flight together, while the first stages of the main loop
+  // are under way. A layer of 3 x 60 tokens, 4096 wide, takes 185 us over 256 cached keys and 189 over 261 (196 when the
+  // wave that held a sequence's first token copied element after element in the epilogue); 1 x 64 over 323: 134 (131
+  // over 320; a copy launch of its own added 4.5).
+  __device__ __forceinline__ void carry(int w0, int bw, int t0, int t1, int Nw, int tid, int nthr) const {
+    const int DH = o.dh, LOG2DH = DH == 128 ? 7 : 6, qrows = o.H * DH, kvrows = o.Hkv * DH;
+    const int w_lo = max(w0, qrows), n = min(w0 + bw, Nw) - w_lo;  // the tile's k and v rows
+    const int b0 = (t0 + o.S - 1) / o.S, nb = (t1 + o.S - 1) / o.S - b0;  // sequences that start in the tile
+    for (int e = tid; e < n * nb; e += nthr) {
+      const int x = e / n, w = w_lo + (e - x * n) - qrows, b = b0 + x;
+      const int key = o.pos0 - o.koff;
+      const bf16_t* src;
+      bf16_t* dst;
+      int ld;  // elements between keys
+      if (w < kvrows) {  // pairs of rows are dimensions jp and jp + DH / 2
+        const size_t head = (size_t)b * o.Hkv + (w >> LOG2DH);
+        const int wl = w & (DH - 1), d = (wl >> 1) + (wl & 1) * (DH >> 1);
+        src = o.kc + (head * o.Pc + key) * DH + d;
+        dst = o.k + head * o.Sk * DH + d;
+        ld = DH;
+      } else {
+        const size_t row = (size_t)b * kvrows + (w - kvrows);
+        src = o.vc + row * o.Pc + key;
+        dst = o.vt + row * o.Sp;
+        ld = 1;
       }
+      bf16_t v[7];
+#pragma unroll
+      for (int z = 0; z < 7; ++z)
+        v[z] = src[min(z, o.koff - 1) * ld];
+      // vmcnt(0) in a form that the compiler counts: with these loads open on some path it would wait for all of the
+      // main loop's DMA wherever that reuses their registers (d5120, 64 tokens: 183 -> 218 us a layer)
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+      for (int z = 0; z < 7; ++z)
+        if (z < o.koff) dst[z * ld] = v[z];
     }
   }
 };
@@ -714,6 +726,8 @@ gemm_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int Nw, 
 #pragma unroll
     for (int st = 0; st < STAGES; ++st)
       if (st < nk) issue(st);
+    if constexpr (Epi::kKind == kEpiQkv)
+      if (epi.o.kc) epi.carry(w0, BW, t0, min(t0 + BT, Tv), Nw, tid, NWAVE * 64);
     wait_stages<IPW, STAGES - 1>(min(STAGES, nk) - 1);  // stage 0 landed
     lds_barrier();
     bf16x8_t fa[2][SW], fb[2][ST];
@@ -900,6 +914,8 @@ gemm_pp_kernel(const bf16_t* __restrict__ W, const bf16_t* __restrict__ X, int N
     for (int i = 0; i < SW; ++i)
 #pragma unroll
       for (int j = 0; j < ST; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if constexpr (Epi::kKind == kEpiQkv)
+      if (epi.o.kc) epi.carry(w0, BW, t0, min(t0 + bt, Tv), Nw, threadIdx.x, 512);
     wait_stages<IPW, S - 1>(min(S, nk) - 1);
     phase_barrier();
     if (late && nk > 0) phase_barrier();

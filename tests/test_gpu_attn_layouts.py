@@ -24,6 +24,7 @@ CASES = [
     (128, 16, 4, 3, 977, 0), (128, 16, 16, 4, 577, 0),                                                  # 4 x 1 x 1
     (128, 16, 4, 4, 833, 0), (128, 32, 4, 6, 289, 35),                                                  # 4 x 2 x 1
     (64, 16, 4, 1, 641, 0), (64, 16, 8, 2, 805, 0), (64, 16, 4, 4, 130, 333), (64, 16, 2, 5, 577, 9),    # 64-key tiles
+    (64, 4, 2, 70, 1, 15), (128, 16, 16, 60, 3, 23),              # more carried rows in a GEMM tile than threads
 ]
 
 
