@@ -1009,7 +1009,7 @@ static const TileCfg kCfgs[] = {
     {128, 192, 64, 4, 2, 4, 1}, {128, 128, 64, 4, 2, 4, 1}, {128, 64, 64, 3, 2, 4, 1},
     // one token tile of weights streamed (stream_cfg)
     {32, 32, 128, 4, 2, 2, 0},  {32, 64, 128, 6, 1, 4, 0},  {48, 64, 128, 5, 1, 4, 0},  {96, 64, 128, 3, 2, 2, 0},
-    {128, 192, 64, 3, 2, 4, 0},  // residual GEMMs with full token tiles (plan_gemm)
+    {128, 192, 64, 3, 2, 4, 0},  // residual GEMMs with full token tiles, heads of one round (plan_gemm)
 };
 constexpr int kModelCfgs = 15;  // the first ones: those that the cost model chooses from
 constexpr int kNumCfgs = sizeof(kCfgs) / sizeof(kCfgs[0]);
@@ -1114,8 +1114,17 @@ GemmPlan plan_gemm(int Nw, int T, int K, int force_bw, int max_split) {
   // 23.7 -> 22.7 us, K = 12288 47.9 -> 47.3, 3584 x 384 x 18944 64.6 -> 63.3; with a partly filled last tile up to 13 %
   // slower, 3584 x 448 x 18944).
   if (best.cfg == 12 && max_split > 1 && (T - 1) % 192 >= 128) best.cfg = 19;
-  const TileCfg& c = kCfgs[best.cfg];
-  best.tiles = ((Nw + c.bw - 1) / c.bw) * ((T + c.bt - 1) / c.bt);
+  auto tiles = [&](int ci) {
+    const TileCfg& c = kCfgs[ci];
+    return ((Nw + c.bw - 1) / c.bw) * ((T + c.bt - 1) / c.bt);
+  };
+  // The LM head of a small vocabulary, where one round of 128 x 192 tiles holds it and the model's choice is 256 x 128 or
+  // 128 x 256 ones: these leave CUs idle or fragments empty, and a unit per CU is bound by the bytes that it has in flight.
+  // 32000 x 4096 at 129 - 192 rows 67 -> 55 us, 16384 x 2048 at 384 rows 38 -> 32, 6000 x 4096 at 900 rows 74 -> 53; of 66
+  // such heads one is slower (14000 x 512, 384 rows: 21.0, 22.1). Where the model takes 128 x 128, 256 x 64 or 128 x 64
+  // tiles those are the faster ones (16384 x 4096, 250 rows: 44, 55 here).
+  if (lm && (best.cfg == 5 || best.cfg == 11) && tiles(19) <= kCUs) best.cfg = 19;
+  best.tiles = tiles(best.cfg);
   return best;
 }
 
@@ -1201,10 +1210,10 @@ static bool run_pp(const bf16_t* W, const bf16_t* X, int Nw, int T, int K, const
 static_assert(kNumCfgs == 20, "run_plan dispatches every configuration of kCfgs");
 
 // Whether the epilogue has a kernel for configuration CI: the LM head runs only the layouts of lm_ok, the debug
-// logits (test support) one tile, and the 128 x 192 ring serves only residual GEMMs.
+// logits (test support) one tile, and the 128 x 192 ring serves residual GEMMs and the LM head.
 template <class Epi, int CI>
 constexpr bool has_cfg() {
-  if (Epi::kKind == kEpiLm) return (CI >= 3 && CI <= 6) || CI == 11 || CI == 13 || CI == 14;
+  if (Epi::kKind == kEpiLm) return (CI >= 3 && CI <= 6) || CI == 11 || CI == 13 || CI == 14 || CI == 19;
   if (Epi::kKind == kEpiDebug) return CI == 13;
   return !lm_only(CI) && (CI != 19 || Epi::kKind == kEpiResid);
 }
