@@ -414,8 +414,14 @@ static void run_attn(const AttnArgs& a, hipStream_t s) {
 //   up to 256 query waves: a workgroup per query wave whose four waves share out the keys: otherwise few CUs have work
 //     at all. 32 (1 x 16 tokens over 1900 keys, kernel alone) 39.2 -> 25.1, head_dim 64, 24 (1 x 96) 4.8 -> 3.8
 //     (up to 64 keys most of those waves would have none: the next layout, 2 - 7 % faster there)
-//   up to 640, without a cache 1024: 32-query workgroups, so more CUs have one: 896 (1 x 448) 16.6 -> 16.2, Dream's (1 x
-//     512) 18.5 -> 17.6; with a cache every workgroup more reads it once more (1024, 8 x 64 over 1216: 10 % slower)
+//   up to 1024 without a cache: 32-query workgroups, so more CUs have one: 896 (1 x 448) 16.6 -> 16.2, Dream's (1 x
+//     512) 18.5 -> 17.6
+//   with a cache every workgroup more reads it once more, so these only where they are a workgroup per CU at most, or two
+//     where workgroups of 64 queries would be two as well (with half their queries empty): 192 (2 x 180 over 1800, 16
+//     heads) 49.0 -> 45.0, 420 for 280 (Dream, 5 x 90 over 975) 39.8 -> 31.2; but 384 for 192 (6 x 40 over 1800) 69.5
+//     against 56.5, 320 for 160 (5 x 40 over 975) 37.3 against 30.9
+//   the other workgroups of 64 queries that are one to a CU, with a cache: four query waves, so that the CU has eight
+//     (5 x 60 over 331 18.4 -> 17.3, 9 x 60 over 1800, 16 heads, 55.9 -> 53.6; 1.6 % on average of 189 sizes)
 //   few keys: one key group, since a group's share would be one to five tiles and the merge: 1092 (3 x 203) 14.7 -> 13.3
 //   up to 512 workgroups of 64 queries, two to a CU: two query fragments per wave and two key groups (2048, 1 x
 //     1024, 40.7 -> 38.2); up to 768, three to a CU: one fragment, one group (2624, 1 x 1300, 78.2 -> 73.3; 3072, 1 x
@@ -425,9 +431,11 @@ static void run_attn(const AttnArgs& a, hipStream_t s) {
 // (1024, 1 x 1024, 20.0 -> 18.7; 2048, 1 x 2048, 48.9 -> 43.9; 3072, 4 x 768, 32.1 -> 29.5); in between 32-query
 // workgroups are (1280, 1 x 1280, 1.10 times as fast).
 // Over 331 sizes (4 to 32 heads, 16 to 3072 tokens, 0 to 2003 cached keys) the rule is on average 0.6 % slower than the
-// fastest of eight layouts, at most 12 % (2304 to 2560 tokens of 28 or 32 heads).
+// fastest of eight layouts, at most 12 % (2304 to 2560 tokens of 28 or 32 heads); over 363 of 12 to 64 heads, 30 to 180
+// tokens per sequence and 331 to 1800 cached keys 0.3 % slower than the fastest of three, at most 10 %.
 void launch_attention(const AttnArgs& a, hipStream_t s) {
   const long query_waves = (long)a.B * a.H * ((a.S + 15) / 16), wg64 = (long)a.B * a.H * ((a.S + 63) / 64);
+  const long wg32 = (long)a.B * a.H * ((a.S + 31) / 32);
   const int nkeys = a.P + (a.Sk ? a.Sk : a.S);
   const bool few = query_waves <= 256 && nkeys > 64;
   if (a.dh == 128) {
@@ -435,7 +443,8 @@ void launch_attention(const AttnArgs& a, hipStream_t s) {
     else if (query_waves > 640 && (query_waves <= 2800 || wg64 <= 768) &&
              (nkeys <= 320 || (query_waves >= 2048 && wg64 > 512)))
       run_attn<4, 1, 1, 32, 128, 2>(a, s);
-    else if (query_waves <= (a.P ? 640 : 1024)) run_attn<2, 1, 2, 32, 128, 2>(a, s);
+    else if (a.P ? wg32 <= 256 || (wg32 <= 512 && wg64 > 256) : query_waves <= 1024) run_attn<2, 1, 2, 32, 128, 2>(a, s);
+    else if (a.P && wg64 <= 256) run_attn<4, 1, 2, 32, 128, 2>(a, s);
     else if (query_waves < 2048 || wg64 <= 512) run_attn<2, 2, 2, 32, 128, 2>(a, s);
     else run_attn<4, 2, 1, 32, 128, 2>(a, s);
   } else {

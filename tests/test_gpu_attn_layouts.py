@@ -19,6 +19,9 @@ CASES = [
     (64, 4, 4, 1, 96, 0), (64, 4, 2, 3, 33, 45), (64, 8, 8, 1, 64, 0), (64, 16, 4, 9, 31, 70),
     (128, 16, 4, 5, 49, 8), (128, 16, 16, 5, 33, 9), (128, 16, 4, 1, 799, 0), (128, 16, 8, 9, 40, 71),  # 2 x 1 x 2
     (128, 16, 4, 15, 47, 0), (128, 16, 16, 15, 33, 270), (128, 16, 4, 3, 700, 0),                       # 4 x 1 x 1
+    (128, 16, 16, 20, 30, 331), (128, 16, 8, 32, 19, 338), (128, 16, 4, 16, 17, 333),                   # 2 x 1 x 2
+    (128, 16, 16, 9, 41, 331), (128, 16, 4, 8, 50, 333), (128, 32, 4, 2, 97, 1217),                    # 4 x 1 x 2
+    (128, 16, 8, 33, 19, 338), (128, 16, 4, 5, 180, 322),                                               # 2 x 2 x 2
     (128, 16, 4, 2, 449, 0), (128, 16, 8, 2, 512, 0),                                                   # 2 x 1 x 2
     (128, 16, 4, 2, 577, 0), (128, 16, 8, 3, 331, 13), (128, 16, 4, 9, 65, 290), (128, 16, 4, 4, 512, 0),  # 2 x 2 x 2
     (128, 16, 4, 3, 977, 0), (128, 16, 16, 4, 577, 0),                                                  # 4 x 1 x 1
