@@ -409,44 +409,45 @@ static void run_attn(const AttnArgs& a, hipStream_t s) {
 }
 
 // Rings of two steps. The layout follows from the query waves (16 queries each) that the call has and from how its
-// workgroups fill 256 CUs of four SIMDs, which hold two (layouts of 2 x 2 waves) or three (4 x 1 x 1) of them. Kernel
-// in the layer, us, cached keys from HBM, against other layouts:
+// workgroups fill the rounds of 256 CUs, which hold two (layouts of 2 x 2 waves) or three (4 x 1 x 1) of them. head_dim
+// 128, kernel in the layer, us, cached keys from HBM:
 //   up to 256 query waves: a workgroup per query wave whose four waves share out the keys: otherwise few CUs have work
 //     at all. 32 (1 x 16 tokens over 1900 keys, kernel alone) 39.2 -> 25.1, head_dim 64, 24 (1 x 96) 4.8 -> 3.8
 //     (up to 64 keys most of those waves would have none: the next layout, 2 - 7 % faster there)
-//   up to 1024 without a cache: 32-query workgroups, so more CUs have one: 896 (1 x 448) 16.6 -> 16.2, Dream's (1 x
-//     512) 18.5 -> 17.6
-//   with a cache every workgroup more reads it once more, so these only where they are a workgroup per CU at most, or two
-//     where workgroups of 64 queries would be two as well (with half their queries empty): 192 (2 x 180 over 1800, 16
-//     heads) 49.0 -> 45.0, 420 for 280 (Dream, 5 x 90 over 975) 39.8 -> 31.2; but 384 for 192 (6 x 40 over 1800) 69.5
-//     against 56.5, 320 for 160 (5 x 40 over 975) 37.3 against 30.9
-//   the other workgroups of 64 queries that are one to a CU, with a cache: four query waves, so that the CU has eight
-//     (5 x 60 over 331 18.4 -> 17.3, 9 x 60 over 1800, 16 heads, 55.9 -> 53.6; 1.6 % on average of 189 sizes)
-//   few keys: one key group, since a group's share would be one to five tiles and the merge: 1092 (3 x 203) 14.7 -> 13.3
-//   up to 512 workgroups of 64 queries, two to a CU: two query fragments per wave and two key groups (2048, 1 x
-//     1024, 40.7 -> 38.2); up to 768, three to a CU: one fragment, one group (2624, 1 x 1300, 78.2 -> 73.3; 3072, 1 x
-//     1536, 86.4 -> 78.8; 4 x 384 30.2 -> 27.2); above, 128 queries (3616, 1 x 1800, 1.15 times as fast as 64).
+//   32-query workgroups while they are one to a CU (192 of them, 2 x 180 over 1800, 16 heads, 49.0 -> 45.0), and two where
+//     workgroups of 64 queries would be two as well, with half their queries empty (420 for 280, Dream, 5 x 90 over 975,
+//     39.8 -> 31.2), or where all keys are fresh and warm (1 x 448 16.6 -> 16.2, 2 x 250 13.9 -> 12.0; up to 160 keys one
+//     key group is 3 % faster). Over a cache the second workgroup reads it once more: 384 for 192 (6 x 40 over 1800) 69.5
+//     against 56.5 with the next layout, 320 for 160 (5 x 40 over 975) 37.3 against 30.9
+//   workgroups of 64 queries, one to a CU, over a cache: four query waves and two key groups, so that the CU has eight
+//     waves (5 x 60 over 331 18.4 -> 17.3; 1.6 % faster than 2 x 2 x 2 on average of 189 sizes)
+//   more than 768 of them: 128-query workgroups (3616 query waves, 1 x 1800, 1.15 times as fast; 16 x 70 over 331 46.4 ->
+//     34.4) unless a sequence's last one would be more than half empty and they are 3/5 as many (up to 64, 129 - 192 or
+//     257 - 320 tokens: 13 x 130 over 700 96.6 against 73.3 with one key group, 32 x 60 21.8 against 17.2)
+//   more than 320 keys and almost two full rounds of two to a CU: as for one (32 x 60 over 331 63.2 -> 56.0)
+//   up to 320 keys one key group, since a group's share would be few tiles and the merge (3 x 203 14.7 -> 13.3), and
+//     where three of its workgroups to a CU beat two (1 x 1300 78.2 -> 73.3, 4 x 384 30.2 -> 27.2); otherwise two
+//     query fragments per wave and two key groups (1 x 1024 40.7 -> 38.2).
 // head_dim 64: 64-key tiles halve the steps of four query waves x two key groups, which is the faster layout over more
 // than 320 keys where 129 to 256 or 385 to 512 of its workgroups fill one round of the CUs, or more than 640 the last one
 // (1024, 1 x 1024, 20.0 -> 18.7; 2048, 1 x 2048, 48.9 -> 43.9; 3072, 4 x 768, 32.1 -> 29.5); in between 32-query
 // workgroups are (1280, 1 x 1280, 1.10 times as fast).
 // Over 331 sizes (4 to 32 heads, 16 to 3072 tokens, 0 to 2003 cached keys) the rule is on average 0.6 % slower than the
-// fastest of eight layouts, at most 12 % (2304 to 2560 tokens of 28 or 32 heads); over 363 of 12 to 64 heads, 30 to 180
-// tokens per sequence and 331 to 1800 cached keys 0.3 % slower than the fastest of three, at most 10 %.
+// fastest of eight layouts, at most 12 % (2304 to 2560 tokens of 28 or 32 heads); over 1000 more of 12 to 64 heads, 1 to
+// 48 sequences of 20 to 320 tokens, without or with 70 to 1800 cached keys, 0.5 %, at most 13 %.
 void launch_attention(const AttnArgs& a, hipStream_t s) {
   const long query_waves = (long)a.B * a.H * ((a.S + 15) / 16), wg64 = (long)a.B * a.H * ((a.S + 63) / 64);
-  const long wg32 = (long)a.B * a.H * ((a.S + 31) / 32);
+  const long wg32 = (long)a.B * a.H * ((a.S + 31) / 32), wg128 = (long)a.B * a.H * ((a.S + 127) / 128);
   const int nkeys = a.P + (a.Sk ? a.Sk : a.S);
   const bool few = query_waves <= 256 && nkeys > 64;
   if (a.dh == 128) {
     if (few) run_attn<1, 1, 4, 32, 128, 2>(a, s);
-    else if (query_waves > 640 && (query_waves <= 2800 || wg64 <= 768) &&
-             (nkeys <= 320 || (query_waves >= 2048 && wg64 > 512)))
-      run_attn<4, 1, 1, 32, 128, 2>(a, s);
-    else if (a.P ? wg32 <= 256 || (wg32 <= 512 && wg64 > 256) : query_waves <= 1024) run_attn<2, 1, 2, 32, 128, 2>(a, s);
-    else if (a.P && wg64 <= 256) run_attn<4, 1, 2, 32, 128, 2>(a, s);
-    else if (query_waves < 2048 || wg64 <= 512) run_attn<2, 2, 2, 32, 128, 2>(a, s);
-    else run_attn<4, 2, 1, 32, 128, 2>(a, s);
+    else if (wg32 <= 256 || (wg32 <= 512 && (wg64 > 256 || (!a.P && nkeys > 160)))) run_attn<2, 1, 2, 32, 128, 2>(a, s);
+    else if (a.P && wg64 <= 256 && nkeys > 160) run_attn<4, 1, 2, 32, 128, 2>(a, s);
+    else if (wg64 > 768 && 5 * wg128 < 3 * wg64) run_attn<4, 2, 1, 32, 128, 2>(a, s);
+    else if (nkeys > 320 && wg64 > 896 && wg64 <= 1024) run_attn<4, 1, 2, 32, 128, 2>(a, s);
+    else if (nkeys <= 320 || wg64 > 512) run_attn<4, 1, 1, 32, 128, 2>(a, s);
+    else run_attn<2, 2, 2, 32, 128, 2>(a, s);
   } else {
     const bool filled = wg64 <= 256 ? wg64 > 128 : wg64 <= 512 ? wg64 > 384 : wg64 > 640;
     if (few) run_attn<1, 1, 4, 32, 64, 2>(a, s);

@@ -17,17 +17,18 @@ import synth
 CASES = [
     (128, 4, 2, 1, 17, 0), (128, 4, 4, 1, 65, 0), (128, 4, 2, 2, 33, 331), (128, 2, 1, 1, 1, 96),       # few
     (64, 4, 4, 1, 96, 0), (64, 4, 2, 3, 33, 45), (64, 8, 8, 1, 64, 0), (64, 16, 4, 9, 31, 70),
-    (128, 16, 4, 5, 49, 8), (128, 16, 16, 5, 33, 9), (128, 16, 4, 1, 799, 0), (128, 16, 8, 9, 40, 71),  # 2 x 1 x 2
-    (128, 16, 4, 15, 47, 0), (128, 16, 16, 15, 33, 270), (128, 16, 4, 3, 700, 0),                       # 4 x 1 x 1
-    (128, 16, 16, 20, 30, 331), (128, 16, 8, 32, 19, 338), (128, 16, 4, 16, 17, 333),                   # 2 x 1 x 2
-    (128, 16, 16, 9, 41, 331), (128, 16, 4, 8, 50, 333), (128, 32, 4, 2, 97, 1217),                    # 4 x 1 x 2
-    (128, 16, 8, 33, 19, 338), (128, 16, 4, 5, 180, 322),                                               # 2 x 2 x 2
-    (128, 16, 4, 2, 449, 0), (128, 16, 8, 2, 512, 0),                                                   # 2 x 1 x 2
-    (128, 16, 4, 2, 577, 0), (128, 16, 8, 3, 331, 13), (128, 16, 4, 9, 65, 290), (128, 16, 4, 4, 512, 0),  # 2 x 2 x 2
-    (128, 16, 4, 3, 977, 0), (128, 16, 16, 4, 577, 0),                                                  # 4 x 1 x 1
-    (128, 16, 4, 4, 833, 0), (128, 32, 4, 6, 289, 35),                                                  # 4 x 2 x 1
+    (128, 16, 4, 5, 49, 8), (128, 16, 16, 5, 33, 9), (128, 16, 4, 1, 799, 0), (128, 16, 4, 2, 449, 0),  # 2 x 1 x 2
+    (128, 16, 8, 2, 512, 0), (128, 16, 4, 9, 65, 290), (128, 16, 16, 20, 30, 331), (128, 16, 8, 32, 19, 338),
+    (128, 16, 4, 16, 17, 333), (128, 16, 4, 8, 50, 333), (128, 32, 4, 2, 97, 1217), (128, 16, 4, 3, 161, 0),
+    (128, 16, 16, 15, 33, 270), (128, 16, 16, 9, 41, 331), (128, 16, 4, 5, 180, 322), (128, 16, 16, 9, 50, 111),  # 4 x 1 x 2
+    (128, 32, 4, 6, 289, 35), (128, 16, 8, 20, 131, 260), (128, 16, 4, 64, 17, 331),
+    (128, 16, 8, 9, 40, 71), (128, 16, 4, 15, 47, 0), (128, 16, 4, 3, 700, 0), (128, 16, 8, 33, 19, 338),  # 4 x 1 x 1
+    (128, 16, 4, 3, 977, 0), (128, 16, 16, 4, 577, 0), (128, 16, 4, 9, 50, 110), (128, 16, 16, 60, 3, 23),
+    (128, 16, 4, 65, 17, 331), (128, 16, 4, 23, 129, 331), (128, 16, 4, 3, 160, 0),
+    (128, 16, 4, 2, 577, 0), (128, 16, 8, 3, 331, 13), (128, 16, 4, 4, 512, 0),                         # 2 x 2 x 2
+    (128, 16, 4, 4, 833, 0), (128, 16, 4, 13, 200, 90), (128, 32, 4, 13, 66, 332), (128, 16, 4, 13, 193, 0),  # 4 x 2 x 1
     (64, 16, 4, 1, 641, 0), (64, 16, 8, 2, 805, 0), (64, 16, 4, 4, 130, 333), (64, 16, 2, 5, 577, 9),    # 64-key tiles
-    (64, 4, 2, 70, 1, 15), (128, 16, 16, 60, 3, 23),              # more carried rows in a GEMM tile than threads
+    (64, 4, 2, 70, 1, 15),                                        # more carried rows in a GEMM tile than threads
 ]
 
 
